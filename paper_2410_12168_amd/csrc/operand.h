@@ -20,6 +20,8 @@ namespace {
 
 typedef int i32x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr uint32_t kSignMag = 0x87878787u;
@@ -50,6 +52,25 @@ __device__ __forceinline__ f32x4 mfma_fp8(const i32x8& a, const i32x8& b, f32x4 
 __device__ __forceinline__ f32x4 mfma_fp8_x8(const i32x8& a, const i32x8& b, f32x4 c) {
   return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a, b, c, 0, 0, 0, (int)0x82828282u, 0,
                                                           0x7F7F7F7F);
+}
+
+// The 32x32x64 forms (a K-block is two of them, chained).
+__device__ __forceinline__ f32x16 mfma32_fp8(const i32x8& a, const i32x8& b, f32x16 c) {
+  return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, 0, 0, 0, 0, 0, 0);
+}
+__device__ __forceinline__ f32x16 mfma32_fp8_x8(const i32x8& a, const i32x8& b, f32x16 c) {
+  return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, 0, 0, 0, (int)0x82828282u, 0,
+                                                          0x7F7F7F7F);
+}
+
+// v_mfma_f32_32x32x8_f16 on one fp16 value per lane (in the low half of x and
+// y; the other three K positions of the lane are zero): element (i, j) of the
+// 32x32 result is x(i) y(j) + x(i + 32) y(j + 32), by lanes.
+__device__ __forceinline__ f32x16 scale_products32(uint32_t x, uint32_t y) {
+  typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+  return __builtin_amdgcn_mfma_f32_32x32x8f16(__builtin_bit_cast(f16x4, u32x2{x, 0u}),
+                                              __builtin_bit_cast(f16x4, u32x2{y, 0u}), f32x16{},
+                                              0, 0, 0);
 }
 
 __device__ __forceinline__ f32x4 scale_products(float sa, float sw) {

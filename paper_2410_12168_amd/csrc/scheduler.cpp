@@ -204,8 +204,8 @@ bool build_plan(int M, int N, int K, int G, const uint8_t* prec, const PlanOptio
 }
 
 // Tile height.  Up to 128 rows a 128-row tile (a taller one would leave MFMA
-// rows idle).  Above that, a 256-row tile does one K-block in about 2.1 us
-// on MI355X against about 1.35 us for a 128-row tile, so per row it is the
+// rows idle).  Above that, a 256-row tile does one K-block in about 1.9 us
+// on MI355X against about 1.22 us for a 128-row tile, so per row it is the
 // cheaper unit of work, but there are half as many tiles.  When that leaves a
 // fractional last wave that the plan splits (build_plan, "cost" mode), the
 // split costs a fixup of about 25 us: every split tile's fp32 partials are
@@ -230,8 +230,8 @@ int choose_tile_m(int M, int N, int K, int G, int cus) {
     }
     return blocks * us_per_block + (split ? 25.0 : 0.0) + extra_us;
   };
-  const double t_large = estimate(kLarge, 2.1, 0.0);
-  const double t_small = estimate(kSmall, 1.35, 4.0);
+  const double t_large = estimate(kLarge, 1.9, 0.0);
+  const double t_small = estimate(kSmall, 1.22, 4.0);
   return t_small < 0.97 * t_large ? kSmall : kLarge;
 }
 
