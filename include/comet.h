@@ -90,8 +90,9 @@ typedef struct ihipStream_t* hipStream_t;
 
 /* GEMM kernels (comet_gemm_kernel). */
 typedef enum {
-  COMET_KERNEL_FEW_TOKEN = 0,         /* one wave per 16 columns and split-K slot */
-  COMET_KERNEL_FEW_TOKEN_SHARED = 1,  /* the same, activations shared through LDS */
+  COMET_KERNEL_FEW_TOKEN = 0,         /* one wave per 16 columns and split-K slot, or, above 8
+                                         rows, 16 waves per 32 columns */
+  COMET_KERNEL_FEW_TOKEN_SHARED = 1,  /* the first, activations shared through LDS, or the second */
   COMET_KERNEL_MID = 2,               /* 128-row tiles */
   COMET_KERNEL_TILE = 3,              /* 256-row tiles */
   COMET_KERNEL_STREAM = 4             /* up to 64 rows, weight panels divided evenly over the CUs */

@@ -2,9 +2,10 @@
 //
 // With a few tokens the GEMM is a weight stream: every 4-bit weight is read
 // from HBM once and used by few activation rows, so the bound is HBM
-// bandwidth, not the matrix cores.  Three designs live here:
+// bandwidth, not the matrix cores.  These designs live here:
 //   * the per-wave and shared-activation kernels (M <= 48, any N), first
-//     below;
+//     below, and the pair kernel, which takes their shapes with 8 < M <= 48
+//     where it is faster (skinny_pair);
 //   * the stream kernels (M <= 64, when the 16-column weight panels divide
 //     evenly over the CUs): each workgroup owns whole panels and streams them
 //     as contiguous runs, at the end of the file.
@@ -539,6 +540,198 @@ hipError_t launch_shared(const GemmArgs& a, bool diag, hipStream_t stream) {
   return hipGetLastError();
 }
 
+
+// ---------------------------------------------------------------------------
+// Few-token kernel over pairs of panels (8 < M <= 48, long K).  The per-wave
+// kernel above gives every wave one panel, so each K-block's activation codes
+// (1 KB per row block) are read and unpacked for one kilobyte of weights; at
+// three row blocks that, not the weight stream, is its time, and with one or
+// two slots a SIMD has one wave to hide it behind.  Here a workgroup of 16
+// waves owns two panels and its waves split K sixteen ways: a wave's activation
+// fragments serve both panels, four waves share a SIMD, and a wave's weights
+// (three K-blocks in flight) are still one contiguous run per panel.  The
+// partial sums are added in slot order through LDS (deterministic, no
+// cross-workgroup traffic).
+constexpr int kPairWaves = 16;
+
+// One K-block's weights of both panels and their scales of column lane % 16.
+struct PairW {
+  u32x4 w[2];
+  uint32_t sw[2];
+};
+__device__ __forceinline__ void pair_w(const GemmArgs& p, int g, int pa, int pb, PairW& x) {
+  int lane = threadIdx.x & 63;
+  asm volatile("" : "+v"(lane));  // not held in registers between steps
+  const int NG = p.K / kG;
+  const uint32_t off = (lane & 15) * 64 + (lane >> 4) * 16;
+  x.w[0] = __builtin_nontemporal_load(
+      reinterpret_cast<const u32x4*>(p.W + ((size_t)pa * NG + g) * 1024 + off));
+  x.w[1] = __builtin_nontemporal_load(
+      reinterpret_cast<const u32x4*>(p.W + ((size_t)pb * NG + g) * 1024 + off));
+  const uint16_t* sw = p.sw + (size_t)g * p.N + (lane & 15);
+  x.sw[0] = sw[16 * pa];
+  x.sw[1] = sw[16 * pb];
+}
+
+template <int R, bool DIAG>
+__global__ __launch_bounds__(kPairWaves * 64) void skinny_pair_kernel(GemmArgs p) {
+  extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+  const int lane = threadIdx.x & 63;
+  const int r16 = lane & 15, q4 = lane >> 4;
+  const int slot = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int NG = p.K / kG, P = p.N / 16;
+  const int pa = 2 * blockIdx.x, pb = min(pa + 1, P - 1);  // the last workgroup may have one panel
+  const int g0 = NG * slot / kPairWaves, g1 = NG * (slot + 1) / kPairWaves;
+  const uint32_t M = p.M;
+
+  f32x4 C[2][R];
+  #pragma unroll
+  for (int h = 0; h < 2; ++h)
+    #pragma unroll
+    for (int r = 0; r < R; ++r) C[h][r] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  if (g0 < g1) {
+    constexpr int D = R < 3 ? 3 : 2;  // K-blocks of weights in flight (registers)
+    PairW w[D];
+    #pragma unroll
+    for (int i = 0; i < D; ++i) pair_w(p, min(g0 + i, g1 - 1), pa, pb, w[i]);
+    int aoff = aoff_of(p, g0);
+    auto step = [&](int g, PairW& x) {
+      // the lane's row offsets are computed anew in each step rather than held
+      int ln = lane;
+      asm volatile("" : "+v"(ln));
+      const uint32_t l16 = ln & 15, lq = ln >> 4;
+      const bool b8 = is8(p, g);
+      const uint32_t s8 = b8 ? 1u : 0u;
+      const uint8_t* A = p.A + (size_t)p.M * 64 * (size_t)aoff;
+      const uint16_t* S = p.sa + (size_t)g * p.M;
+      aoff += 1 + (int)s8;
+      // activation fragments (row 16 r + lane % 16, codes 32 (lane / 16) ..) and
+      // scales (row 16 r + 4 (lane / 16) + lane % 4, see scale_products)
+      u32x4 a[R];
+      uint32_t sa[R];
+      auto addr = [&](int r) {
+        return (min(16u * r + l16, M - 1) << (6 + s8)) + (lq << (4 + s8));
+      };
+      #pragma unroll
+      for (int r = 0; r < R; ++r) {
+        a[r] = *reinterpret_cast<const u32x4*>(A + addr(r));
+        sa[r] = S[min(16u * r + 4 * lq + (ln & 3), M - 1)];
+      }
+      i32x8 wf[2];
+      float sw[2];
+      #pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        u32x4 lo, hi;
+        unpack4(x.w[h], lo, hi);
+        wf[h] = i32x8{(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3],
+                      (int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
+        sw[h] = __half2float(__ushort_as_half((unsigned short)x.sw[h]));
+      }
+      issue_point();
+      pair_w(p, min(g + D, g1 - 1), pa, pb, x);  // behind the activations: their wait leaves it in flight
+      issue_point();
+      #pragma unroll
+      for (int r = 0; r < R; ++r) {
+        f32x4 y[2];
+        if (b8) {
+          // the second 16 bytes of the lane's codes, read here: few blocks need them
+          const u32x4 a1 = *reinterpret_cast<const u32x4*>(A + addr(r) + 16);
+          i32x8 al, ah;
+          #pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            al[k] = (int)lo8(a[r][k]);
+            al[4 + k] = (int)lo8(a1[k]);
+            ah[k] = (int)hi8(a[r][k]);
+            ah[4 + k] = (int)hi8(a1[k]);
+          }
+          // exact: integers below 2^24 units
+          #pragma unroll
+          for (int h = 0; h < 2; ++h)
+            y[h] = mfma_fp8_x8(ah, wf[h], mfma_fp8(al, wf[h], f32x4{0.f, 0.f, 0.f, 0.f}));
+        } else {
+          u32x4 lo, hi;
+          unpack4(a[r], lo, hi);
+          const i32x8 af = {(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3],
+                            (int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
+          #pragma unroll
+          for (int h = 0; h < 2; ++h) y[h] = mfma_fp8(af, wf[h], f32x4{0.f, 0.f, 0.f, 0.f});
+        }
+        const float s = __half2float(__ushort_as_half((unsigned short)sa[r])) * kUnit;
+        __builtin_amdgcn_sched_barrier(0);  // keep row blocks apart: fewer live registers
+        #pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          if constexpr (DIAG) {
+            const int col = 16 * (h ? pb : pa) + r16;
+            #pragma unroll
+            for (int k = 0; k < 4; ++k) {
+              const int row = 16 * r + 4 * q4 + k;
+              if (row >= p.win_m0 && row < p.win_m1 && col >= p.win_n0 && col < p.win_n1) {
+                const size_t idx = ((size_t)(row - p.win_m0) * (p.win_n1 - p.win_n0) +
+                                    (col - p.win_n0)) * NG + g;
+                p.acc[idx] = (int32_t)(y[h][k] * kUnit);
+              }
+            }
+          } else {
+            const f32x4 Q = scale_products(s, sw[h]);
+            #pragma unroll
+            for (int k = 0; k < 4; ++k) C[h][r][k] = __builtin_fmaf(y[h][k], Q[k], C[h][r][k]);
+          }
+        }
+      }
+    };
+    for (int g = g0; g < g1; g += D) {
+      #pragma unroll
+      for (int i = 0; i < D; ++i)
+        if (g + i < g1) step(g + i, w[i]);
+    }
+  }
+  if constexpr (DIAG) return;
+
+  f32x4* red = reinterpret_cast<f32x4*>(smem);  // [slot][2 R][64]
+  #pragma unroll
+  for (int h = 0; h < 2; ++h)
+    #pragma unroll
+    for (int r = 0; r < R; ++r) red[(slot * 2 * R + h * R + r) * 64 + lane] = C[h][r];
+  __syncthreads();
+  const int item = threadIdx.x >> 6;  // (panel, row block)
+  if (item >= 2 * R) return;
+  f32x4 acc = red[item * 64 + lane];
+  #pragma unroll
+  for (int s = 1; s < kPairWaves; ++s) acc += red[(s * 2 * R + item) * 64 + lane];
+  const int h = item / R, r = item % R;
+  if (pa + h >= P) return;
+  #pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int row = 16 * r + 4 * q4 + k;
+    if (row < p.M)
+      p.out[(size_t)row * p.N + 16 * (pa + h) + r16] = __half_as_ushort(__float2half_rn(acc[k]));
+  }
+}
+
+template <int R>
+const void* pair_fn(bool diag) {
+  return diag ? reinterpret_cast<const void*>(&skinny_pair_kernel<R, true>)
+              : reinterpret_cast<const void*>(&skinny_pair_kernel<R, false>);
+}
+const void* pair_kernel(int R, bool diag) {
+  return R == 1 ? pair_fn<1>(diag) : R == 2 ? pair_fn<2>(diag) : pair_fn<3>(diag);
+}
+
+// Whether the pair kernel takes this few-token shape: at least two K-blocks a
+// wave, and enough pairs for half of the CUs but no second round of
+// workgroups.  Measured at 256 CUs (us, per-wave or shared kernel -> pairs):
+// K = 28672, 512 panels: M = 16 36.6 -> 27.3, 32 51.7 -> 33.9, 48 65.4 -> 39.3;
+// K = 8192, 512 panels: 13.2 -> 12.3, 17.3 -> 14.3, 21.5 -> 15.0; K = 4096, 384
+// panels: 7.7 -> 7.2, 24 rows 10.1 -> 8.0, 12.4 -> 8.5; K = 14336, 256 panels:
+// 13.8 -> 13.3, 20.0 -> 19.2.  Below 256 panels it loses at 16 rows (8.8 -> 9.7
+// with 234), above 512 too (24 rows, 528 panels: 18.7 -> 20.4), but not at 48
+// rows, where the per-wave kernel is furthest from the weight stream (640
+// panels 27.0 -> 25.0, 1024 39.4 -> 28.4; at 33 rows, 768 panels, 24.4 -> 25.2).
+bool skinny_pair(int M, int N, int K, int cus) {
+  const int P = N / 16;
+  return M > 8 && K / kG >= 2 * kPairWaves && P >= cus && (P <= 2 * cus || M > 40);
+}
 
 // ---------------------------------------------------------------------------
 // Few-token stream kernel (M <= 8).  W_packed's 16-row panels make the whole
@@ -1295,6 +1488,13 @@ hipError_t set_skinny_attributes() {
     hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kStreamMaxLds);
     if (e != hipSuccess) return e;
   }
+  for (int R : {1, 2, 3})
+    for (bool diag : {false, true}) {
+      hipError_t e = hipFuncSetAttribute(pair_kernel(R, diag),
+                                         hipFuncAttributeMaxDynamicSharedMemorySize,
+                                         kPairWaves * 2 * R * 64 * 16);
+      if (e != hipSuccess) return e;
+    }
   for (int R : {1, 2, 3, 4})
     for (bool diag : {false, true}) {
       hipError_t e = hipFuncSetAttribute(chunk_kernel(R, diag),
@@ -1335,6 +1535,14 @@ hipError_t launch_gemm_skinny(const GemmArgs& a, bool diag, hipStream_t stream) 
     return hipGetLastError();
   }
 
+  if (skinny_pair(a.M, a.N, a.K, a.cus)) {
+    const int R = (a.M + 15) / 16;
+    if (R > 3) return hipErrorInvalidValue;
+    GemmArgs args = a;
+    void* params[] = {&args};
+    return hipLaunchKernel(pair_kernel(R, diag), dim3((a.N / 16 + 1) / 2), dim3(kPairWaves * 64),
+                           params, kPairWaves * 2 * R * 64 * 16, stream);
+  }
   if (a.splits < 1 || kWaves % a.splits != 0) return hipErrorInvalidValue;
   // 8 < M <= 32: the shared-activation kernel.  At M <= 8 the per-wave kernel
   // is faster: it needs fewer registers (four waves per SIMD against three),

@@ -1,0 +1,35 @@
+"""The pair kernel of the few-token GEMM (8 < M <= 48, two weight panels per
+workgroup, K split over its sixteen waves): row-block edges, an odd panel count,
+uneven slots and 8-bit blocks, against the CPU oracle; exact block sums of a
+window; and the same bits on a second call.
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2410_12168_amd as comet
+import synth
+from parity import assert_out_close
+from test_gpu_parity import dev_u16, host, host_u16
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("M", [9, 16, 17, 32, 33, 48])
+@pytest.mark.parametrize("panels,NG,n8", [(256, 32, 2), (257, 33, 33), (512, 47, 0), (601, 32, 5)])
+def test_pair_kernel(M, panels, NG, n8):
+    N, K = 16 * panels, 128 * NG
+    prec = synth.prec_map(NG, n8, "random", seed=M)
+    print(f"M={M} N={N} K={K} n8={n8}", flush=True)
+    x16, w16 = synth.activations(M, M, K, prec), synth.weights(panels, N, K)
+    A, sa = comet.quantize_act(dev_u16(x16), prec)
+    Wp, sw = comet.pack_w4(dev_u16(w16))
+    out = comet.w4ax_gemm(A, prec, sa, Wp, sw, M, N, K)
+    qa, s_a = oracle.quantize_act(x16, prec)
+    qw, s_w = oracle.quantize_weight(w16)
+    assert_out_close(host_u16(out).view(np.float16), oracle.dequant_gemm(qa, s_a, qw, s_w), f"M={M}")
+    assert torch.equal(out, comet.w4ax_gemm(A, prec, sa, Wp, sw, M, N, K))
+    n0 = N - 24  # crosses the last two panels
+    acc = comet.w4ax_gemm_acc(A, prec, sa, Wp, sw, M, N, K, M - 3, M, n0, N)
+    assert np.array_equal(host(acc), oracle.group_acc(qa[M - 3:], qw[n0:]))
