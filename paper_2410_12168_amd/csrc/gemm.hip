@@ -12,10 +12,10 @@
 // needs no int->float convert.
 // Dequantization (Sec. 4.3: the scale absorbs the conversion factor), once per
 // output and K-block:
-//     C += Y * P,   P = sa * sw      (fp32; sa * sw is exact),
-// with P from one v_mfma_f32_32x32x8_f16 per block (K = 1 of 8 used), which
-// leaves one vector operation per output; C is kept in units of 2^-18, scaled
-// once at the end.
+//     C += Y * P,   P = 2 sa * sw    (fp32; exact),
+// with P from one v_mfma_f32_32x32x8_f16 per block (K = 2 of 8 used, twice the
+// same product), which leaves one vector operation per output; C is kept in
+// units of 2^-17, scaled once at the end.
 //
 // What bounds it: a SIMD issues MFMAs and vector operations in turn more than
 // side by side.  A 16x16x128 MFMA with the eight vector operations of its
@@ -379,8 +379,8 @@ __device__ __forceinline__ i32x8 unpack_frag(u32x4 v) {
 
 __device__ __forceinline__ void order_point() { __builtin_amdgcn_sched_barrier(0); }
 
-// Accumulators of a wave's quadrant, in units of 2^-18 (the FP8 code
-// encoding), and the block whose dequantization is still due, the last one of
+// Accumulators of a wave's quadrant, in units of 2^-17 (the FP8 code
+// encoding, and P = 2 sa sw, see scale_products32), and the block whose dequantization is still due, the last one of
 // the K-block before: C[NB - 1] += y * P.  Block b is row block b / CB, column
 // block b % CB.
 template <int TM>
@@ -437,18 +437,8 @@ __device__ __forceinline__ void store_sums(const GemmArgs& p, const f32x16& y, i
 struct Frags {
   i32x8 wf[2][2];
   i32x8 af[2];
-  uint32_t sa, sw;
+  uint32_t sa, sw[2];  // one fp16 scale each, the upper half zero
 };
-
-// Scale products of a 32 x 32 block: one v_mfma_f32_32x32x8_f16 with the
-// scales in K-group 0 (lanes 0-31).  The B operand holds both column blocks'
-// scales, as K = 0 and 1; the A operand holds the row's scale as K = cb, so
-// the second column block's is the first's shifted by 16 bits.
-__device__ __forceinline__ uint32_t weight_scales(const uint8_t* sw) {
-  const uint32_t s0 = *reinterpret_cast<const uint16_t*>(sw);
-  const uint32_t s1 = *reinterpret_cast<const uint16_t*>(sw + 64);
-  return (opaque_tid() & 32) ? 0u : s0 | (s1 << 16);
-}
 
 // The compute phase of one K-block: RB x 2 blocks of 32 x 32 of the wave's
 // quadrant, from the fragments in f, the activation stage and the scale slot
@@ -466,7 +456,7 @@ __device__ __forceinline__ void compute4(const uint8_t* a, const uint8_t* sap, F
                                          int g, const GemmArgs& p, const TileLoads& t,
                                          Acc<TM>& acc, Hook&& hook) {
   constexpr int RB = Geo<TM>::RB, CB = Geo<TM>::CB, NB = RB * CB;
-  if constexpr (!DIAG) acc.P = scale_products32(f.sa, f.sw);
+  if constexpr (!DIAG) acc.P = scale_products32(f.sa, f.sw[0]);
   order_point();
   i32x8 an[2];  // the next row block, read a whole row block ahead
   #pragma unroll
@@ -497,9 +487,8 @@ __device__ __forceinline__ void compute4(const uint8_t* a, const uint8_t* sap, F
       if (b > 0) {
         acc.template dequant<4, 16>(b - 1);
         order_point();
-        acc.P = scale_products32(f.sa, f.sw);
+        acc.P = scale_products32(f.sa, f.sw[cb]);
       }
-      if (cb == 0) f.sa <<= 16;
       if (last_cb) f.sa = *reinterpret_cast<const uint32_t*>(sap + (rb + 1) * 128);
       acc.y = y;
     }
@@ -523,8 +512,7 @@ __device__ __forceinline__ void compute8(const uint8_t* const (&a)[2], const uin
     const int rb = b / CB, cb = b % CB;
     const bool last_cb = cb == CB - 1 && rb + 1 < RB;
     f32x16 y = {};
-    if constexpr (!DIAG) acc.P = scale_products32(f.sa, f.sw);
-    if (cb == 0) f.sa <<= 16;
+    if constexpr (!DIAG) acc.P = scale_products32(f.sa, f.sw[cb]);
     if (last_cb) f.sa = *reinterpret_cast<const uint32_t*>(sap + (rb + 1) * 128);
     #pragma unroll
     for (int h = 0; h < 2; ++h) {
@@ -610,7 +598,8 @@ __device__ __forceinline__ void kloop_phases(const GemmArgs& p, uint8_t* smem, u
       raw[cb][0] = *reinterpret_cast<const u32x4*>(w + o.w + cb * 2048);
       raw[cb][1] = *reinterpret_cast<const u32x4*>(w + (o.w ^ 32) + cb * 2048);
     }
-    f.sw = weight_scales(w + o.sw);
+    #pragma unroll
+    for (int cb = 0; cb < 2; ++cb) f.sw[cb] = *reinterpret_cast<const uint16_t*>(w + o.sw + 64 * cb);
     f.sa = *reinterpret_cast<const uint32_t*>(sap);
     f.af[0] = lds_frag(a + aunit(0, 0, 0), a + aunit(0, 0, 1));
     f.af[1] = lds_frag(a + aunit(0, 1, 0), a + aunit(0, 1, 1));
@@ -697,7 +686,8 @@ __device__ __forceinline__ void kloop_step(const GemmArgs& p, uint8_t* smem, uin
     Frags f;
     u32x4 raw[2][2];
     f.sa = *reinterpret_cast<const uint32_t*>(sap);
-    f.sw = weight_scales(w + o.sw);
+    #pragma unroll
+    for (int cb = 0; cb < 2; ++cb) f.sw[cb] = *reinterpret_cast<const uint16_t*>(w + o.sw + 64 * cb);
     raw[0][0] = *reinterpret_cast<const u32x4*>(w + o.w);
     if constexpr (!B8) f.af[0] = lds_frag(a[0] + aunit(0, 0, 0), a[0] + aunit(0, 0, 1));
     raw[0][1] = *reinterpret_cast<const u32x4*>(w + (o.w ^ 32));
@@ -791,9 +781,9 @@ __device__ __forceinline__ int block_row(int rb, int q2, int i) {
   return rb * 32 + 8 * (i >> 2) + 4 * q2 + (i & 3);
 }
 
-// An accumulator (units of 2^-18) as fp16.
+// An accumulator (units of 2^-17) as fp16.
 __device__ __forceinline__ uint16_t out_f16(float c) {
-  return __half_as_ushort(__float2half_rn(c * kUnit));
+  return __half_as_ushort(__float2half_rn(c * (kUnit / 2)));
 }
 
 // Epilogue of a work unit: a whole tile is stored as fp16; a split tile

@@ -63,9 +63,12 @@ __device__ __forceinline__ f32x16 mfma32_fp8_x8(const i32x8& a, const i32x8& b, 
                                                           0x7F7F7F7F);
 }
 
-// v_mfma_f32_32x32x8_f16 on one fp16 value per lane (in the low half of x and
-// y; the other three K positions of the lane are zero): element (i, j) of the
-// 32x32 result is x(i) y(j) + x(i + 32) y(j + 32), by lanes.
+// v_mfma_f32_32x32x8_f16 on one fp16 scale per lane (in the low half of x and
+// y; the other three K positions of the lane are zero in both): element (i, j)
+// of the 32x32 result is x(i) y(j) + x(i + 32) y(j + 32), by lanes.  Lanes l
+// and l + 32 hold the same scale, so it is 2 x(i) y(j), exactly.  No scale
+// meets another row's or column's, nor a zero: an infinite or NaN scale stays
+// in its own row or column.
 __device__ __forceinline__ f32x16 scale_products32(uint32_t x, uint32_t y) {
   typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
   return __builtin_amdgcn_mfma_f32_32x32x8f16(__builtin_bit_cast(f16x4, u32x2{x, 0u}),

@@ -59,3 +59,32 @@ def test_subnormal_scales(M, N):
     s = np.asarray(sa).view(np.float16).astype(np.float32)
     assert 0 < s.max() < 6.1e-5
     assert_out_close(run(M, N, prec, x16, w16), reference(prec, x16, w16), "subnormal scales")
+
+
+@pytest.mark.parametrize("M,N", [(100, 256), (513, 2064)])
+@pytest.mark.parametrize("bad", [np.inf, np.nan])
+def test_scale_not_finite(M, N, bad):
+    # one infinite or NaN scale: every other row and column keeps its bits, and its
+    # own has (block sum) * scale: signed infinities, NaN where the sum is 0
+    prec = np.array([4, 8, 4], np.uint8)
+    K = 384
+    x16, w16 = synth.activations(3, M, K, prec), synth.weights(3, N, K)
+    A, sa = comet.quantize_act(dev_u16(x16), prec)
+    Wp, sw = comet.pack_w4(dev_u16(w16))
+    good = comet.w4ax_gemm(A, prec, sa, Wp, sw, M, N, K)
+    for row, col, g in ((7, None, 0), (40, None, 1), (None, 5, 1), (None, 40, 2), (None, N - 1, 0)):
+        s_a, s_w = sa.clone(), sw.clone()
+        if col is None:
+            s_a[g, row] = bad
+            own = (slice(row, row + 1), slice(0, N))
+        else:
+            s_w[g, col] = bad
+            own = (slice(0, M), slice(col, col + 1))
+        print(f"M={M} N={N} {bad} row={row} col={col} block={g}", flush=True)
+        out = comet.w4ax_gemm(A, prec, s_a, Wp, s_w, M, N, K)
+        acc = comet.w4ax_gemm_acc(A, prec, sa, Wp, sw, M, N, K, own[0].start, own[0].stop,
+                                  own[1].start, own[1].stop)
+        want = good.clone()
+        want[own] = (acc[..., g].float() * bad).half()
+        assert torch.equal(torch.isnan(out), torch.isnan(want))
+        assert torch.equal(out.nan_to_num(0, 60000, -60000), want.nan_to_num(0, 60000, -60000))
