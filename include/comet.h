@@ -94,7 +94,9 @@ typedef enum {
                                          rows, 16 waves per 32 columns */
   COMET_KERNEL_FEW_TOKEN_SHARED = 1,  /* the first, activations shared through LDS, or the second */
   COMET_KERNEL_MID = 2,               /* 128-row tiles */
-  COMET_KERNEL_TILE = 3,              /* 256-row tiles */
+  COMET_KERNEL_TILE = 3,              /* 256-row tiles; these two also name the shapes of up to 256
+                                         rows that, short of tiles, run 16 waves per 32 columns and
+                                         48 rows */
   COMET_KERNEL_STREAM = 4             /* up to 64 rows, weight panels divided evenly over the CUs */
 } comet_kernel_t;
 

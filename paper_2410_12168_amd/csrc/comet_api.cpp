@@ -178,7 +178,8 @@ std::string sched_mode() {
 // M <= 48, except that above 32 rows the 128-row tile kernel takes over when
 // its 256-column tiles cover at least 3/4 of the CUs (wide N); the 128-row
 // tile kernel runs up to M = 128; above, comet::choose_tile_m picks 128 or
-// 256 rows from the shape.
+// 256 rows from the shape.  Shapes of the tile kernels that have too few tiles
+// for the CUs run as row groups of the pair kernel instead (in_row_groups).
 int kernel_kind(int M, int N, int K, int cus) {
   if (comet::skinny_stream_eligible(M, N, K, cus)) return COMET_KERNEL_STREAM;
   const int col_tiles = (N + comet::kTileN - 1) / comet::kTileN;
@@ -189,6 +190,17 @@ int kernel_kind(int M, int N, int K, int cus) {
                : COMET_KERNEL_FEW_TOKEN;
   return comet::choose_tile_m(M, N, K, comet::kG, cus) == comet::kTileMSmall ? COMET_KERNEL_MID
                                                                              : COMET_KERNEL_TILE;
+}
+
+// Whether a shape of kernel_kind `kind` runs on the few-token kernels: they walk
+// the K-blocks in natural order and need no plan and no workspace.
+bool in_row_groups(int kind, int M, int N, int K, int cus) {
+  return (kind == COMET_KERNEL_MID || kind == COMET_KERNEL_TILE) && M > comet::kSkinnyMaxM &&
+         comet::row_groups_pay(M, N, K, comet::kG, cus);
+}
+bool few_token(int kind, int M, int N, int K, int cus) {
+  return kind == COMET_KERNEL_FEW_TOKEN || kind == COMET_KERNEL_FEW_TOKEN_SHARED ||
+         kind == COMET_KERNEL_STREAM || in_row_groups(kind, M, N, K, cus);
 }
 
 comet::PlanOptions plan_options(int M, int N, int K, int cus, const std::string& mode) {
@@ -373,9 +385,7 @@ comet_status_t run_gemm(const uint8_t* A, const uint8_t* prec, const uint16_t* s
   }
   const bool diag = acc != nullptr;
   const int kind = kernel_kind(M, N, K, info.cus);
-  const bool skinny = kind == COMET_KERNEL_FEW_TOKEN || kind == COMET_KERNEL_FEW_TOKEN_SHARED ||
-                      kind == COMET_KERNEL_STREAM;
-  // the few-token kernels walk the K-blocks in natural order and need no plan
+  const bool skinny = few_token(kind, M, N, K, info.cus);
   const DevicePlan* plan = nullptr;
   // the fused SwiGLU epilogue has no natural-order form: it takes "dp" instead
   std::string mode = sched_mode();
@@ -423,7 +433,7 @@ comet_status_t run_gemm(const uint8_t* A, const uint8_t* prec, const uint16_t* s
   // standalone SwiGLU quantizer is faster (the epilogue's exp and division
   // then run on the whole chip at once, not on one tile's waves after its
   // K-loop), so the GEMM writes fp16 to the stream's workspace first.
-  if (swiglu && kind != COMET_KERNEL_MID) {
+  if (swiglu && (skinny || kind != COMET_KERNEL_MID)) {
     uint16_t* tmp;
     if ((st = get_tmp(dev, stream, (size_t)M * N * sizeof(uint16_t), &tmp))) return st;
     a.out = tmp;
@@ -485,8 +495,7 @@ comet_status_t run_gemm_noalloc(const uint8_t* A, const uint8_t* prec, const uin
   a.cus = info.cus;
   a.map = map;
   for (int g = 0; g < K / comet::kG; ++g) a.n4 += prec[g] == 4;
-  if (kind == COMET_KERNEL_FEW_TOKEN || kind == COMET_KERNEL_FEW_TOKEN_SHARED ||
-      kind == COMET_KERNEL_STREAM) {
+  if (few_token(kind, M, N, K, info.cus)) {
     a.splits = comet::skinny_splits(N, K, info.cus);
     return launched(comet::launch_gemm_skinny(a, false, stream), "gemm launch");
   }

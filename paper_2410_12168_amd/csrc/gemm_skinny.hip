@@ -5,7 +5,8 @@
 // bandwidth, not the matrix cores.  These designs live here:
 //   * the per-wave and shared-activation kernels (M <= 48, any N), first
 //     below, and the pair kernel, which takes their shapes with 8 < M <= 48
-//     where it is faster (skinny_pair);
+//     where it is faster (skinny_pair), and up to 256 rows in groups of 48
+//     where few panels leave the tile kernels short of tiles (row_groups_pay);
 //   * the stream kernels (M <= 64, when the 16-column weight panels divide
 //     evenly over the CUs): each workgroup owns whole panels and streams them
 //     as contiguous runs, at the end of the file.
@@ -542,7 +543,7 @@ hipError_t launch_shared(const GemmArgs& a, bool diag, hipStream_t stream) {
 
 
 // ---------------------------------------------------------------------------
-// Few-token kernel over pairs of panels (8 < M <= 48, long K).  The per-wave
+// Few-token kernel over pairs of panels (M > 8, long K).  The per-wave
 // kernel above gives every wave one panel, so each K-block's activation codes
 // (1 KB per row block) are read and unpacked for one kilobyte of weights; at
 // three row blocks that, not the weight stream, is its time, and with one or
@@ -552,6 +553,10 @@ hipError_t launch_shared(const GemmArgs& a, bool diag, hipStream_t stream) {
 // (three K-blocks in flight) are still one contiguous run per panel.  The
 // partial sums are added in slot order through LDS (deterministic, no
 // cross-workgroup traffic).
+// More rows go in groups of up to 48 (blockIdx.y) where row_groups_pay says so:
+// with few weight panels the 128- and 256-row tiles are too few for the CUs, and
+// the partial tiles they are cut into cost more than reading weights and
+// activation codes again from the caches.
 constexpr int kPairWaves = 16;
 
 // One K-block's weights of both panels and their scales of column lane % 16.
@@ -583,6 +588,7 @@ __global__ __launch_bounds__(kPairWaves * 64) void skinny_pair_kernel(GemmArgs p
   const int pa = 2 * blockIdx.x, pb = min(pa + 1, P - 1);  // the last workgroup may have one panel
   const int g0 = NG * slot / kPairWaves, g1 = NG * (slot + 1) / kPairWaves;
   const uint32_t M = p.M;
+  const int m0 = 16 * R * blockIdx.y;
 
   f32x4 C[2][R];
   #pragma unroll
@@ -606,17 +612,17 @@ __global__ __launch_bounds__(kPairWaves * 64) void skinny_pair_kernel(GemmArgs p
       const uint8_t* A = p.A + (size_t)p.M * 64 * (size_t)aoff;
       const uint16_t* S = p.sa + (size_t)g * p.M;
       aoff += 1 + (int)s8;
-      // activation fragments (row 16 r + lane % 16, codes 32 (lane / 16) ..) and
-      // scales (row 16 r + 4 (lane / 16) + lane % 4, see scale_products)
+      // activation fragments (row m0 + 16 r + lane % 16, codes 32 (lane / 16) ..) and
+      // scales (row m0 + 16 r + 4 (lane / 16) + lane % 4, see scale_products)
       u32x4 a[R];
       uint32_t sa[R];
       auto addr = [&](int r) {
-        return (min(16u * r + l16, M - 1) << (6 + s8)) + (lq << (4 + s8));
+        return (min(m0 + 16u * r + l16, M - 1) << (6 + s8)) + (lq << (4 + s8));
       };
       #pragma unroll
       for (int r = 0; r < R; ++r) {
         a[r] = *reinterpret_cast<const u32x4*>(A + addr(r));
-        sa[r] = S[min(16u * r + 4 * lq + (ln & 3), M - 1)];
+        sa[r] = S[min(m0 + 16u * r + 4 * lq + (ln & 3), M - 1)];
       }
       i32x8 wf[2];
       float sw[2];
@@ -665,7 +671,7 @@ __global__ __launch_bounds__(kPairWaves * 64) void skinny_pair_kernel(GemmArgs p
             const int col = 16 * (h ? pb : pa) + r16;
             #pragma unroll
             for (int k = 0; k < 4; ++k) {
-              const int row = 16 * r + 4 * q4 + k;
+              const int row = m0 + 16 * r + 4 * q4 + k;
               if (row >= p.win_m0 && row < p.win_m1 && col >= p.win_n0 && col < p.win_n1) {
                 const size_t idx = ((size_t)(row - p.win_m0) * (p.win_n1 - p.win_n0) +
                                     (col - p.win_n0)) * NG + g;
@@ -703,7 +709,7 @@ __global__ __launch_bounds__(kPairWaves * 64) void skinny_pair_kernel(GemmArgs p
   if (pa + h >= P) return;
   #pragma unroll
   for (int k = 0; k < 4; ++k) {
-    const int row = 16 * r + 4 * q4 + k;
+    const int row = m0 + 16 * r + 4 * q4 + k;
     if (row < p.M)
       p.out[(size_t)row * p.N + 16 * (pa + h) + r16] = __half_as_ushort(__float2half_rn(acc[k]));
   }
@@ -732,6 +738,8 @@ bool skinny_pair(int M, int N, int K, int cus) {
   const int P = N / 16;
   return M > 8 && K / kG >= 2 * kPairWaves && P >= cus && (P <= 2 * cus || M > 40);
 }
+
+constexpr int kPairMaxR = 3;  // row blocks of a row group (four would spill)
 
 // ---------------------------------------------------------------------------
 // Few-token stream kernel (M <= 8).  W_packed's 16-row panels make the whole
@@ -1535,13 +1543,14 @@ hipError_t launch_gemm_skinny(const GemmArgs& a, bool diag, hipStream_t stream) 
     return hipGetLastError();
   }
 
-  if (skinny_pair(a.M, a.N, a.K, a.cus)) {
-    const int R = (a.M + 15) / 16;
-    if (R > 3) return hipErrorInvalidValue;
+  if (a.M > kSkinnyMaxM || skinny_pair(a.M, a.N, a.K, a.cus)) {
+    // row groups of equal height (one up to 48 rows), as row_groups_pay counts them
+    const int rb = (a.M + 15) / 16, ny = (rb + kPairMaxR - 1) / kPairMaxR;
+    const int R = (rb + ny - 1) / ny;
     GemmArgs args = a;
     void* params[] = {&args};
-    return hipLaunchKernel(pair_kernel(R, diag), dim3((a.N / 16 + 1) / 2), dim3(kPairWaves * 64),
-                           params, kPairWaves * 2 * R * 64 * 16, stream);
+    return hipLaunchKernel(pair_kernel(R, diag), dim3((a.N / 16 + 1) / 2, (rb + R - 1) / R),
+                           dim3(kPairWaves * 64), params, kPairWaves * 2 * R * 64 * 16, stream);
   }
   if (a.splits < 1 || kWaves % a.splits != 0) return hipErrorInvalidValue;
   // 8 < M <= 32: the shared-activation kernel.  At M <= 8 the per-wave kernel

@@ -94,7 +94,8 @@ hipError_t launch_swiglu_quantize(const uint16_t* GU, uint8_t* A, uint16_t* sa, 
 // 8 < M <= 64 the K-blocks go in chunks whose activation fragments are staged
 // in LDS.  Otherwise (M <= kSkinnyMaxM) one wave per (16 columns, split-K
 // slot), or, for 8 < M <= 32 with at most two slots, four column blocks per
-// workgroup sharing the activation operand through LDS.
+// workgroup sharing the activation operand through LDS, or pairs of panels;
+// above kSkinnyMaxM only pairs, in row groups (row_groups_pay).
 constexpr int kSkinnyMaxM = 48;
 constexpr int kStreamMaxLds = 160 * 1024;
 bool skinny_stream_eligible(int M, int N, int K, int cus);

@@ -203,36 +203,44 @@ bool build_plan(int M, int N, int K, int G, const uint8_t* prec, const PlanOptio
   return true;
 }
 
+// What the tile kernels take, in us on MI355X, with tiles of `tm` rows: per
+// workgroup the K-blocks it runs, ~4 us of prologue and epilogue per tile, and,
+// when the plan splits tiles (build_plan, "cost" mode), the fixup.  A split
+// tile's fp32 partials are written and read back at the end of the launch by
+// its last workgroup, so with 256 rows the fixup grows with the slots per tile:
+// 8192 x 8192 at 256 rows, eight slots, 62.8 us (45.5 with 128 rows), 4096 x
+// 4096, sixteen, 70.0 (34.8).  Fitted to ten layers at 160 to 2000 rows, each
+// with both heights: standard deviation 6 to 8%.  Below eight K-blocks nothing
+// was measured and a fixup counts the same for both.
+static double tile_us(int tm, int M, int N, int K, int G, int cus) {
+  constexpr int kTileCols = 256;
+  const PlanOptions defaults;
+  const bool small = tm <= 128;
+  const long long NG = K / G, P = cus;
+  const long long T = (long long)((M + tm - 1) / tm) * ((N + kTileCols - 1) / kTileCols);
+  const long long waves = (T + P - 1) / P;
+  long long blocks = waves * NG;
+  double fixup = 0;
+  if (T % P != 0 && (double)(P - T % P) / P > defaults.split_min_idle) {
+    blocks = (T * NG + P - 1) / P;
+    const long long sk = T >= P ? T % P + P : T;  // tiles that are split
+    const double slots = std::max(2.0, std::min((double)P, sk * NG / 2.0) / sk);
+    fixup = NG < 8 ? 25 : small ? 26 : 34 + 1.4 * slots;
+  }
+  return blocks * (small ? 1.18 : 1.74) + 4.0 * waves + fixup;
+}
+
 // Tile height.  Up to 128 rows a 128-row tile (a taller one would leave MFMA
-// rows idle).  Above that, a 256-row tile does one K-block in about 1.9 us
-// on MI355X against about 1.22 us for a 128-row tile, so per row it is the
-// cheaper unit of work, but there are half as many tiles.  When that leaves a
-// fractional last wave that the plan splits (build_plan, "cost" mode), the
-// split costs a fixup of about 25 us: every split tile's fp32 partials are
-// written and read back at the end of the launch, all at once.  The estimate
-// below prices both heights that way (per workgroup: the K-blocks it runs,
-// plus the fixup if any tile is split, plus ~4 us more prologue and epilogue
-// for the smaller tile) and keeps 256 rows unless 128 is 3% faster: e.g.
-// 2048 x 4096 x 4096 on 256 CUs has 128 tiles of 256 rows, each split in
+// rows idle).  Above that a 256-row tile is the cheaper unit of work per row,
+// but there are half as many, and a fractional last wave of them is split over
+// more workgroups each: 256 rows unless 128 is 3% faster by the estimate above,
+// e.g. 2048 x 4096 x 4096 on 256 CUs has 128 tiles of 256 rows, each split in
 // two, or 256 tiles of 128 rows, one per workgroup.
 int choose_tile_m(int M, int N, int K, int G, int cus) {
-  constexpr int kSmall = 128, kLarge = 256, kTileCols = 256;
+  constexpr int kSmall = 128, kLarge = 256;
   if (M <= kSmall || cus <= 0 || G <= 0) return M <= kSmall ? kSmall : kLarge;
-  const PlanOptions defaults;
-  const long long NG = K / G, P = cus;
-  auto estimate = [&](int tm, double us_per_block, double extra_us) {
-    const long long T = (long long)((M + tm - 1) / tm) * ((N + kTileCols - 1) / kTileCols);
-    bool split = false;
-    long long blocks = (T + P - 1) / P * NG;
-    if (T % P != 0 && (double)(P - T % P) / P > defaults.split_min_idle) {
-      split = true;
-      blocks = (T * NG + P - 1) / P;
-    }
-    return blocks * us_per_block + (split ? 25.0 : 0.0) + extra_us;
-  };
-  const double t_large = estimate(kLarge, 1.9, 0.0);
-  const double t_small = estimate(kSmall, 1.22, 4.0);
-  return t_small < 0.97 * t_large ? kSmall : kLarge;
+  return tile_us(kSmall, M, N, K, G, cus) < 0.97 * tile_us(kLarge, M, N, K, G, cus) ? kSmall
+                                                                                     : kLarge;
 }
 
 int skinny_splits(int N, int K, int cus) {
@@ -253,6 +261,25 @@ int skinny_splits(int N, int K, int cus) {
     }
   }
   return best;
+}
+
+// Row groups of the pair kernel, for more rows than one group holds: 16 waves
+// a workgroup split the K-blocks, and a round of workgroups takes ~0.8 us and
+// 2.3 (two row blocks) or 2.65 us (three) per K-block of a wave, the weights
+// coming from the caches for the second group on.  They are taken where that is
+// 20% below the tile kernel's estimate, a margin for maps with many 8-bit blocks
+// (half of them: +20% here, +5% there).  Measured at 256 CUs (us, tiles -> row
+// groups): 4096 x 4096 at 64 / 128 / 256 rows 38.5 -> 7.8, 39.5 -> 14.3,
+// 34.8 -> 20.7; K = 14336, N = 4096 at 64 rows 46.3 -> 16.1; 8192 x 8192 at 64 /
+// 96 rows 40.0 -> 25.4, 39.7 -> 28.3, but at 128 rows with half of the blocks
+// 8-bit 43.3 -> 45.9.  More than 256 rows were not measured in full.
+bool row_groups_pay(int M, int N, int K, int G, int cus) {
+  if (cus <= 0 || M > 256 || K / G < 8) return false;
+  const int rb = (M + 15) / 16, ny = (rb + 2) / 3, R = (rb + ny - 1) / ny;
+  const long long wgs = (long long)((rb + R - 1) / R) * ((N / 16 + 1) / 2);
+  const double per_wave = (K / G + 15) / 16;
+  const double pairs = 2.0 + (double)((wgs + cus - 1) / cus) * (0.8 + (R > 2 ? 2.65 : 2.3) * per_wave);
+  return 1.25 * pairs < tile_us(choose_tile_m(M, N, K, G, cus), M, N, K, G, cus);
 }
 
 }  // namespace comet

@@ -69,5 +69,8 @@ bool build_plan(int M, int N, int K, int G, const uint8_t* prec, const PlanOptio
 // 256-column tiles: 128 up to 128 rows, else 256 unless 128-row tiles are
 // estimated clearly faster (see scheduler.cpp).
 int choose_tile_m(int M, int N, int K, int G, int cus);
+// Whether the few-token pair kernel, in groups of up to 48 rows, is estimated
+// clearly faster than the tile kernels (see scheduler.cpp).
+bool row_groups_pay(int M, int N, int K, int G, int cus);
 
 }  // namespace comet
