@@ -44,7 +44,10 @@
 // Measured (LLaMA-3-70B, 1/16 of the blocks 8-bit, back to back, against
 // 16x16x128 MFMAs with P on the vector ALU and one barrier per K-block for both
 // tiles): gate_up at 4096 tokens 1895 -> 1783 us, qkv 351 -> 317 us; gate_up at
-// 128 tokens 88.3 -> 84.5 us; LLaMA-3-8B o at 1900 tokens 47.8 -> 44.9 us.
+// 128 tokens 88.3 -> 84.5 us; LLaMA-3-8B o at 1900 tokens 47.8 -> 44.9 us.  One
+// scale operand per column block (scale_products32) in place of both side by
+// side took gate_up with its quantizer from 1767 to 1728 us at 4096 tokens and
+// from 86.0 to 82.6 us at 128.
 #include <hip/hip_runtime.h>
 #include <hip/hip_fp16.h>
 #include <stdint.h>
