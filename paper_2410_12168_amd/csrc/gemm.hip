@@ -156,16 +156,18 @@ __device__ __forceinline__ int opaque_tid() {
 // per-lane byte offset; the wave's 64 chunks land at LDS bytes lds .. lds +
 // 1023, lane by lane.  Issued as inline assembly so that the compiler does
 // not wait for it at LDS reads of other buffers; the K-loop waits for it
-// explicitly before the barrier that publishes it.
+// explicitly before the barrier that publishes it.  The load must not follow the
+// write of M0 directly, and within inline assembly nothing is put between them
+// but what stands there: the s_nop.
 __device__ __forceinline__ void dma16(const uint8_t* base, uint32_t voff, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1"
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
                :: "v"(voff), "s"(base), "s"(__builtin_amdgcn_readfirstlane(lds)) : "m0");
 }
 // The same with the non-temporal hint, for data used once (the weights of a
 // single row of tiles): it does not displace the activation codes, which
 // every workgroup reads, from L2.
 __device__ __forceinline__ void dma16nt(const uint8_t* base, uint32_t voff, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1 nt"
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt"
                :: "v"(voff), "s"(base), "s"(__builtin_amdgcn_readfirstlane(lds)) : "m0");
 }
 // dma16 of N kilobytes in a row, in memory and in LDS (the instruction's offset
@@ -174,19 +176,19 @@ template <int N>
 __device__ __forceinline__ void dma16_run(const uint8_t* base, uint32_t voff, uint32_t lds) {
   static_assert(N == 2 || N == 4, "runs");
   if constexpr (N == 4)
-    asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1\n\t"
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1\n\t"
                  "global_load_lds_dwordx4 %0, %1 offset:1024\n\t"
                  "global_load_lds_dwordx4 %0, %1 offset:2048\n\t"
                  "global_load_lds_dwordx4 %0, %1 offset:3072"
                  :: "v"(voff), "s"(base), "s"(__builtin_amdgcn_readfirstlane(lds)) : "m0");
   else
-    asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1\n\t"
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1\n\t"
                  "global_load_lds_dwordx4 %0, %1 offset:1024"
                  :: "v"(voff), "s"(base), "s"(__builtin_amdgcn_readfirstlane(lds)) : "m0");
 }
 // 16 bits per lane, zero-extended: lane l's lands at LDS bytes lds + 4 l .. + 3.
 __device__ __forceinline__ void dma2(const uint8_t* base, uint32_t voff, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_ushort %0, %1"
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_ushort %0, %1"
                :: "v"(voff), "s"(base), "s"(__builtin_amdgcn_readfirstlane(lds)) : "m0");
 }
 
