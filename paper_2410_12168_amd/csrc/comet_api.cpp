@@ -146,7 +146,6 @@ struct PlanKey {
 
 struct DevicePlan {
   comet::Plan host;
-  std::vector<int> blob;  // the uploaded array, kept: the copy is asynchronous
   void* dmem = nullptr;  // units | wg_begin | order | split_index, one allocation
   const comet::WorkUnit* units = nullptr;
   const int* wg_begin = nullptr;
@@ -166,6 +165,23 @@ struct Workspace {
 std::map<PlanKey, DevicePlan> g_plans;
 std::map<std::pair<int, hipStream_t>, Workspace> g_ws;
 std::map<int, bool> g_attr_set;
+std::map<int, hipStream_t> g_setup_streams;
+
+// A stream of the library's own on device `dev` for one-time set-up.  What it
+// does is shared by all of the caller's streams, which have no order among one
+// another, so every use is waited for; the caller's work is not.  It is never
+// part of a capture.  Caller holds g_mu.
+hipError_t setup_stream(int dev, hipStream_t* out) {
+  auto it = g_setup_streams.find(dev);
+  if (it == g_setup_streams.end()) {
+    hipStream_t s;
+    hipError_t e = hipStreamCreateWithFlags(&s, hipStreamNonBlocking);
+    if (e != hipSuccess) return e;
+    it = g_setup_streams.emplace(dev, s).first;
+  }
+  *out = it->second;
+  return hipSuccess;
+}
 
 std::string sched_mode() {
   const char* m = std::getenv("COMET_SCHED");
@@ -247,7 +263,7 @@ PlanBlob plan_blob(const comet::Plan& h, const uint8_t* prec) {
 // Plan for (device, shape, map, mode), built and uploaded on first use.
 // Caller holds g_mu.
 comet_status_t get_plan(int dev, int cus, int M, int N, int K, const uint8_t* prec,
-                        const comet::BlockMap& map, const std::string& mode, hipStream_t stream,
+                        const comet::BlockMap& map, const std::string& mode,
                         const DevicePlan** out) {
   PlanKey key{dev, M, N, K, cus, mode, map};
   auto it = g_plans.find(key);
@@ -259,15 +275,17 @@ comet_status_t get_plan(int dev, int cus, int M, int N, int K, const uint8_t* pr
   std::string err;
   if (!comet::build_plan(M, N, K, comet::kG, prec, plan_options(M, N, K, cus, mode), &dp.host, &err))
     return fail(COMET_ERR_INVALID_ARG, "%s", err.c_str());
-  PlanBlob b = plan_blob(dp.host, prec);
-  dp.blob = std::move(b.v);
+  const PlanBlob b = plan_blob(dp.host, prec);
+  const size_t bytes = b.v.size() * sizeof(int);
   if (std::getenv("COMET_TEST_FAIL_ALLOC")) return fail(COMET_ERR_OOM, "plan allocation failed (forced)");
-  hipError_t e = hipMalloc(&dp.dmem, dp.blob.size() * sizeof(int));
+  hipError_t e = hipMalloc(&dp.dmem, bytes);
   if (e != hipSuccess) return fail(COMET_ERR_OOM, "plan allocation: %s", hipGetErrorString(e));
-  // enqueued on the call's stream ahead of the kernel that reads it; the
-  // host array lives in the cache entry, so nobody waits for the copy
-  e = hipMemcpyAsync(dp.dmem, dp.blob.data(), dp.blob.size() * sizeof(int),
-                     hipMemcpyHostToDevice, stream);
+  // in place before the entry is published: the next call with this key may come
+  // on any stream
+  hipStream_t setup;
+  e = setup_stream(dev, &setup);
+  if (e == hipSuccess) e = hipMemcpyAsync(dp.dmem, b.v.data(), bytes, hipMemcpyHostToDevice, setup);
+  if (e == hipSuccess) e = hipStreamSynchronize(setup);
   if (e != hipSuccess) {
     (void)hipFree(dp.dmem);
     return fail(COMET_ERR_HIP, "plan upload: %s", hipGetErrorString(e));
@@ -390,7 +408,7 @@ comet_status_t run_gemm(const uint8_t* A, const uint8_t* prec, const uint16_t* s
   // the fused SwiGLU epilogue has no natural-order form: it takes "dp" instead
   std::string mode = sched_mode();
   if (swiglu && mode == "natural") mode = "dp";
-  if (!skinny && (st = get_plan(dev, info.cus, M, N, K, prec, map, mode, stream, &plan)))
+  if (!skinny && (st = get_plan(dev, info.cus, M, N, K, prec, map, mode, &plan)))
     return st;
   comet::GemmArgs a{};
   a.splits = skinny ? comet::skinny_splits(N, K, info.cus) : 1;
@@ -840,9 +858,14 @@ void comet_release_caches(void) {
     (void)hipFree(kv.second.counters);
     (void)hipFree(kv.second.tmp);
   }
+  for (auto& kv : g_setup_streams) {
+    (void)hipSetDevice(kv.first);
+    (void)hipStreamDestroy(kv.second);
+  }
   if (cur >= 0) (void)hipSetDevice(cur);
   g_plans.clear();
   g_ws.clear();
+  g_setup_streams.clear();
   g_attr_set.clear();
   g_devices.clear();
 }
