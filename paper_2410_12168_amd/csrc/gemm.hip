@@ -163,12 +163,28 @@ __device__ __forceinline__ void dma16(const uint8_t* base, uint32_t voff, uint32
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
                :: "v"(voff), "s"(base), "s"(__builtin_amdgcn_readfirstlane(lds)) : "m0");
 }
-// The same with the non-temporal hint, for data used once (the weights of a
-// single row of tiles): it does not displace the activation codes, which
-// every workgroup reads, from L2.
-__device__ __forceinline__ void dma16nt(const uint8_t* base, uint32_t voff, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt"
-               :: "v"(voff), "s"(base), "s"(__builtin_amdgcn_readfirstlane(lds)) : "m0");
+// Four kilobytes side by side in LDS, each from its own scalar base: one write of
+// M0, and the instruction's offset, which counts for memory and for LDS, so base i
+// is 1024 * i short of its kilobyte.  NT: with the non-temporal hint, for data used
+// once (the weights of a single row of tiles), which then does not displace the
+// activation codes, which every workgroup reads, from L2.
+template <bool NT>
+__device__ __forceinline__ void dma16_from4(const uint8_t* const (&b)[4], uint32_t voff,
+                                            uint32_t lds) {
+  if constexpr (NT)
+    asm volatile("s_mov_b32 m0, %5\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt\n\t"
+                 "global_load_lds_dwordx4 %0, %2 offset:1024 nt\n\t"
+                 "global_load_lds_dwordx4 %0, %3 offset:2048 nt\n\t"
+                 "global_load_lds_dwordx4 %0, %4 offset:3072 nt"
+                 :: "v"(voff), "s"(b[0]), "s"(b[1]), "s"(b[2]), "s"(b[3]),
+                    "s"(__builtin_amdgcn_readfirstlane(lds)) : "m0");
+  else
+    asm volatile("s_mov_b32 m0, %5\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1\n\t"
+                 "global_load_lds_dwordx4 %0, %2 offset:1024\n\t"
+                 "global_load_lds_dwordx4 %0, %3 offset:2048\n\t"
+                 "global_load_lds_dwordx4 %0, %4 offset:3072"
+                 :: "v"(voff), "s"(b[0]), "s"(b[1]), "s"(b[2]), "s"(b[3]),
+                    "s"(__builtin_amdgcn_readfirstlane(lds)) : "m0");
 }
 // dma16 of N kilobytes in a row, in memory and in LDS (the instruction's offset
 // counts for both).
@@ -225,17 +241,17 @@ __device__ __forceinline__ LaneOffsets lane_offsets() {
 // stored).
 struct TileLoads {
   int m0, n0;
-  const uint8_t* w;     // first panel
-  uint32_t dw[3];       // byte offsets of the others from it
+  const uint8_t* w[4];  // panel i, less 1024 * i (dma16_from4)
 };
 template <int TM>
 __device__ __forceinline__ TileLoads tile_loads(const GemmArgs& p, int m0, int n0) {
   using L = Geo<TM>;
   const int NG = p.K / kG, last = p.N / 16 - 1;
   const int p0 = min(n0 / 16 + L::PW * (wave_id() % L::LW), last);
-  TileLoads t{m0, n0, p.W + (size_t)p0 * NG * 1024, {}};
+  static_assert(L::PW == 4, "panels of a weight wave");
+  TileLoads t{m0, n0, {}};
   #pragma unroll
-  for (int i = 0; i < L::PW - 1; ++i) t.dw[i] = (uint32_t)(min(p0 + i + 1, last) - p0) * NG * 1024u;
+  for (int i = 0; i < L::PW; ++i) t.w[i] = p.W + (size_t)min(p0 + i, last) * NG * 1024 - 1024 * i;
   return t;
 }
 
@@ -252,15 +268,7 @@ __device__ __forceinline__ void load_weights(const GemmArgs& p, const TileLoads&
   const int w = wave_id() % L::LW, lane = opaque_tid() & 63;
   const uint32_t g = code & 1023;
   const uint32_t off = (lane >> 2) * 64u + ((lane ^ (lane >> 4)) & 3) * 16u + g * 1024u;
-  const uint32_t dst = slot + L::PW * 1024 * w;
-  #pragma unroll
-  for (int i = 0; i < L::PW; ++i) {
-    const uint32_t o = i ? off + t.dw[i - 1] : off;
-    if constexpr (TM == 128)
-      dma16nt(t.w, o, dst + 1024 * i);
-    else
-      dma16(t.w, o, dst + 1024 * i);
-  }
+  dma16_from4<TM == 128>(t.w, off, slot + L::PW * 1024 * w);
   constexpr int C = kTileN / L::LW;  // columns
   if (lane < C / 8)
     dma16(reinterpret_cast<const uint8_t*>(p.sw + (uint64_t)g * (uint32_t)p.N),
