@@ -65,7 +65,8 @@
  *     the few-token kernels (small M) need no plan.
  *   - The environment variable COMET_SCHED selects the schedule mode (Sec.
  *     4.4, read at every call): "cost" (default: precision-batched K order,
- *     data-parallel full waves of tiles, the last wave split by cost),
+ *     data-parallel full waves of tiles, the last wave split by cost; up to
+ *     256 rows the pair kernel instead where there are too few tiles),
  *     "dp" (precision-batched order, whole tiles only) or "natural" (the
  *     map's own K order, whole tiles only: no tile remapping and no tile
  *     decomposition; the fused SwiGLU entry point takes "dp" instead).

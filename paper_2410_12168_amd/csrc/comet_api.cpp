@@ -209,14 +209,16 @@ int kernel_kind(int M, int N, int K, int cus) {
 }
 
 // Whether a shape of kernel_kind `kind` runs on the few-token kernels: they walk
-// the K-blocks in natural order and need no plan and no workspace.
-bool in_row_groups(int kind, int M, int N, int K, int cus) {
+// the K-blocks in natural order and need no plan and no workspace.  Row groups
+// are part of the "cost" mode; the other modes are schedules of the tile kernels
+// and run on them (build_plan refuses a mode it does not know).
+bool in_row_groups(int kind, int M, int N, int K, int cus, const std::string& mode) {
   return (kind == COMET_KERNEL_MID || kind == COMET_KERNEL_TILE) && M > comet::kSkinnyMaxM &&
-         comet::row_groups_pay(M, N, K, comet::kG, cus);
+         mode == "cost" && comet::row_groups_pay(M, N, K, comet::kG, cus);
 }
-bool few_token(int kind, int M, int N, int K, int cus) {
+bool few_token(int kind, int M, int N, int K, int cus, const std::string& mode) {
   return kind == COMET_KERNEL_FEW_TOKEN || kind == COMET_KERNEL_FEW_TOKEN_SHARED ||
-         kind == COMET_KERNEL_STREAM || in_row_groups(kind, M, N, K, cus);
+         kind == COMET_KERNEL_STREAM || in_row_groups(kind, M, N, K, cus, mode);
 }
 
 comet::PlanOptions plan_options(int M, int N, int K, int cus, const std::string& mode) {
@@ -403,10 +405,10 @@ comet_status_t run_gemm(const uint8_t* A, const uint8_t* prec, const uint16_t* s
   }
   const bool diag = acc != nullptr;
   const int kind = kernel_kind(M, N, K, info.cus);
-  const bool skinny = few_token(kind, M, N, K, info.cus);
+  std::string mode = sched_mode();
+  const bool skinny = few_token(kind, M, N, K, info.cus, mode);
   const DevicePlan* plan = nullptr;
   // the fused SwiGLU epilogue has no natural-order form: it takes "dp" instead
-  std::string mode = sched_mode();
   if (swiglu && mode == "natural") mode = "dp";
   if (!skinny && (st = get_plan(dev, info.cus, M, N, K, prec, map, mode, &plan)))
     return st;
@@ -513,7 +515,8 @@ comet_status_t run_gemm_noalloc(const uint8_t* A, const uint8_t* prec, const uin
   a.cus = info.cus;
   a.map = map;
   for (int g = 0; g < K / comet::kG; ++g) a.n4 += prec[g] == 4;
-  if (few_token(kind, M, N, K, info.cus)) {
+  std::string mode = sched_mode();
+  if (few_token(kind, M, N, K, info.cus, mode)) {
     a.splits = comet::skinny_splits(N, K, info.cus);
     return launched(comet::launch_gemm_skinny(a, false, stream), "gemm launch");
   }
@@ -521,7 +524,6 @@ comet_status_t run_gemm_noalloc(const uint8_t* A, const uint8_t* prec, const uin
   hipError_t e = comet::noalloc_scratch(dev, &ws);
   if (e != hipSuccess)
     return fail(COMET_ERR_HIP, "workspace address (hipGetSymbolAddress): %s", hipGetErrorString(e));
-  std::string mode = sched_mode();
   comet::Plan h;
   std::string err;
   if (!comet::build_plan(M, N, K, comet::kG, prec, plan_options(M, N, K, info.cus, mode), &h, &err))

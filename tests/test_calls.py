@@ -32,3 +32,27 @@ print(json.dumps(out))
     for l in (b, c):
         assert not any(x.startswith("memcpy") for x in l)
         assert any(x.startswith("launch") for x in l)
+
+
+@pytest.mark.parametrize("entry", ["comet_w4ax_gemm", "comet_w4ax_gemm_noalloc"])
+def test_schedule_mode_reaches_shapes_of_row_groups(shim, entry):
+    # 49 to 256 rows of a layer with few panels: row groups by default; the modes
+    # that name a schedule of the tile kernels run it, an unknown one is refused
+    body = f"""
+out = {{}}
+for mode in ("", "cost", "dp", "natural", "bogus"):
+    os.environ["COMET_SCHED"] = mode
+    st = gemm(100, 2048, 2048, entry="{entry}")
+    out[mode] = [st, [l.split()[2] for l in log() if l.startswith("launch")], comet.comet_last_error()]
+print(json.dumps(out))
+"""
+    out = hip_record.run(shim, body)
+    for mode in ("", "cost"):
+        st, kernels, _ = out[mode]
+        assert st == 0 and len(kernels) == 1 and "skinny_pair_kernel" in kernels[0]
+    for mode, natural in (("dp", 0), ("natural", 1)):
+        st, kernels, _ = out[mode]
+        assert st == 0 and len(kernels) == 1
+        assert f"gemm_kernelILi128ELb0ELb0ELb{natural}E" in kernels[0]
+    st, kernels, error = out["bogus"]
+    assert st == 1 and not kernels and "unknown mode bogus" in error
