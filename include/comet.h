@@ -92,14 +92,13 @@ typedef struct ihipStream_t* hipStream_t;
 
 /* GEMM kernels (comet_gemm_kernel). */
 typedef enum {
-  COMET_KERNEL_FEW_TOKEN = 0,         /* one wave per 16 columns and split-K slot, or, above 8
-                                         rows, 16 waves per 32 columns */
-  COMET_KERNEL_FEW_TOKEN_SHARED = 1,  /* the first, activations shared through LDS, or the second */
+  COMET_KERNEL_FEW_TOKEN = 0,         /* one wave per 16 columns and split-K slot */
+  COMET_KERNEL_FEW_TOKEN_SHARED = 1,  /* the same, activations shared through LDS */
   COMET_KERNEL_MID = 2,               /* 128-row tiles */
-  COMET_KERNEL_TILE = 3,              /* 256-row tiles; these two also name the shapes of up to 256
-                                         rows that, short of tiles, run 16 waves per 32 columns and
-                                         48 rows */
-  COMET_KERNEL_STREAM = 4             /* up to 64 rows, weight panels divided evenly over the CUs */
+  COMET_KERNEL_TILE = 3,              /* 256-row tiles */
+  COMET_KERNEL_STREAM = 4,            /* up to 64 rows, weight panels divided evenly over the CUs */
+  COMET_KERNEL_PAIR = 5               /* 16 waves per 32 columns: 9 to 48 rows, and up to 256 in
+                                         groups of at most 48 */
 } comet_kernel_t;
 
 typedef enum {
@@ -293,9 +292,10 @@ COMET_API comet_status_t comet_w4ax_gemm_acc(const uint8_t* A_packed, const uint
                                    int G, int m0, int m1, int n0, int n1, hipStream_t stream);
 
 /* Host-only view of the per-block-precision tile schedule (Sec. 4.4: tile
- * remapping and tile decomposition) that comet_w4ax_gemm would use for this
- * shape and map on `num_cus` compute units.  Nothing is launched and no device
- * is touched.  Each work unit is five ints {tile, g_begin, g_end, slot, nslots}:
+ * remapping and tile decomposition) that the tile kernels would use for this
+ * shape and map on `num_cus` compute units; comet_w4ax_gemm runs it where
+ * comet_gemm_kernel() says COMET_KERNEL_MID or COMET_KERNEL_TILE (the others
+ * have no schedule).  Nothing is launched and no device is touched.  Each work unit is five ints {tile, g_begin, g_end, slot, nslots}:
  * output tile `tile` (row-major over the tile grid), blocks [g_begin, g_end)
  * in the schedule's block order, written as partial `slot` of `nslots`
  * (nslots == 1: the unit owns the whole tile).  Units are listed per
@@ -308,8 +308,9 @@ COMET_API comet_status_t comet_schedule_query(int M, int N, int K, int G, const 
                                     int* tile_m, int* tile_n);
 
 /* Host-only: which GEMM kernel (comet_kernel_t) comet_w4ax_gemm runs for this
- * shape on a device with `num_cus` compute units, or -1 for invalid
- * arguments (comet_last_error() says why).  Nothing is launched. */
+ * shape, in the current COMET_SCHED mode, on a device with `num_cus` compute
+ * units, or -1 for invalid arguments (comet_last_error() says why).  Nothing is
+ * launched. */
 COMET_API int comet_gemm_kernel(int M, int N, int K, int G, int num_cus);
 
 /* SHA-256 (64 hex digits) of the sources and build flags the library was

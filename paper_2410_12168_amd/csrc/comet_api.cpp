@@ -188,38 +188,37 @@ std::string sched_mode() {
   return (m && *m) ? std::string(m) : std::string("cost");
 }
 
-// Which GEMM kernel runs for this shape on `cus` compute units.  The stream
+// Which GEMM kernel runs for this shape on `cus` compute units in schedule mode
+// `mode`: the one decision, for the launches as for comet_gemm_kernel.  The stream
 // kernels take M <= 64 when the weight panels divide evenly over the CUs
 // (and each wave gets enough of them).  Otherwise the few-token kernels take
-// M <= 48, except that above 32 rows the 128-row tile kernel takes over when
-// its 256-column tiles cover at least 3/4 of the CUs (wide N); the 128-row
-// tile kernel runs up to M = 128; above, comet::choose_tile_m picks 128 or
-// 256 rows from the shape.  Shapes of the tile kernels that have too few tiles
-// for the CUs run as row groups of the pair kernel instead (in_row_groups).
-int kernel_kind(int M, int N, int K, int cus) {
+// M <= 48, the pair kernel where skinny_pair finds it faster, except that above
+// 32 rows the 128-row tile kernel takes over when its 256-column tiles cover at
+// least 3/4 of the CUs (wide N).  Above 48 rows the pair kernel takes the shapes
+// that have too few tiles for the CUs, in row groups (row_groups_pay); it is part
+// of the "cost" mode: the other modes are schedules of the tile kernels and run on
+// them (build_plan refuses a mode it does not know).  The 128-row tile kernel runs
+// the rest up to M = 128; above, comet::choose_tile_m picks 128 or 256 rows.
+int kernel_kind(int M, int N, int K, int cus, const std::string& mode) {
   if (comet::skinny_stream_eligible(M, N, K, cus)) return COMET_KERNEL_STREAM;
   const int col_tiles = (N + comet::kTileN - 1) / comet::kTileN;
   const bool wide = 4 * col_tiles >= 3 * cus;
-  if (M <= comet::kSkinnyMaxM && !(M > kSkinnyWideM && wide))
+  if (M <= comet::kSkinnyMaxM && !(M > kSkinnyWideM && wide)) {
+    if (comet::skinny_pair(M, N, K, cus)) return COMET_KERNEL_PAIR;
     return comet::skinny_shared(M, comet::skinny_splits(N, K, cus))
                ? COMET_KERNEL_FEW_TOKEN_SHARED
                : COMET_KERNEL_FEW_TOKEN;
+  }
+  if (M > comet::kSkinnyMaxM && mode == "cost" &&
+      comet::row_groups_pay(M, N, K, comet::kG, cus))
+    return COMET_KERNEL_PAIR;
   return comet::choose_tile_m(M, N, K, comet::kG, cus) == comet::kTileMSmall ? COMET_KERNEL_MID
                                                                              : COMET_KERNEL_TILE;
 }
 
-// Whether a shape of kernel_kind `kind` runs on the few-token kernels: they walk
-// the K-blocks in natural order and need no plan and no workspace.  Row groups
-// are part of the "cost" mode; the other modes are schedules of the tile kernels
-// and run on them (build_plan refuses a mode it does not know).
-bool in_row_groups(int kind, int M, int N, int K, int cus, const std::string& mode) {
-  return (kind == COMET_KERNEL_MID || kind == COMET_KERNEL_TILE) && M > comet::kSkinnyMaxM &&
-         mode == "cost" && comet::row_groups_pay(M, N, K, comet::kG, cus);
-}
-bool few_token(int kind, int M, int N, int K, int cus, const std::string& mode) {
-  return kind == COMET_KERNEL_FEW_TOKEN || kind == COMET_KERNEL_FEW_TOKEN_SHARED ||
-         kind == COMET_KERNEL_STREAM || in_row_groups(kind, M, N, K, cus, mode);
-}
+// The kernels that walk the K-blocks in natural order and need no plan and no
+// workspace.
+bool few_token(int kind) { return kind != COMET_KERNEL_MID && kind != COMET_KERNEL_TILE; }
 
 comet::PlanOptions plan_options(int M, int N, int K, int cus, const std::string& mode) {
   comet::PlanOptions opt;
@@ -404,9 +403,9 @@ comet_status_t run_gemm(const uint8_t* A, const uint8_t* prec, const uint16_t* s
     g_attr_set[dev] = true;
   }
   const bool diag = acc != nullptr;
-  const int kind = kernel_kind(M, N, K, info.cus);
   std::string mode = sched_mode();
-  const bool skinny = few_token(kind, M, N, K, info.cus, mode);
+  const int kind = kernel_kind(M, N, K, info.cus, mode);
+  const bool skinny = few_token(kind);
   const DevicePlan* plan = nullptr;
   // the fused SwiGLU epilogue has no natural-order form: it takes "dp" instead
   if (swiglu && mode == "natural") mode = "dp";
@@ -458,7 +457,7 @@ comet_status_t run_gemm(const uint8_t* A, const uint8_t* prec, const uint16_t* s
     if ((st = get_tmp(dev, stream, (size_t)M * N * sizeof(uint16_t), &tmp))) return st;
     a.out = tmp;
     if (skinny)
-      st = launched(comet::launch_gemm_skinny(a, false, stream), "gemm launch");
+      st = launched(comet::launch_gemm_skinny(a, kind == COMET_KERNEL_PAIR, false, stream), "gemm launch");
     else
       st = launched(comet::launch_gemm(a, plan->host.num_wgs, false, false, mode == "natural",
                                        plan->host.tile_m, stream),
@@ -473,7 +472,7 @@ comet_status_t run_gemm(const uint8_t* A, const uint8_t* prec, const uint16_t* s
     a.out_sa = swiglu->sa;
     a.out_map = swiglu->map;
   }
-  if (skinny) return launched(comet::launch_gemm_skinny(a, diag, stream), "gemm launch");
+  if (skinny) return launched(comet::launch_gemm_skinny(a, kind == COMET_KERNEL_PAIR, diag, stream), "gemm launch");
   return launched(comet::launch_gemm(a, plan->host.num_wgs, diag, swiglu != nullptr,
                                      mode == "natural", plan->host.tile_m, stream),
                   "gemm launch");
@@ -502,7 +501,8 @@ comet_status_t run_gemm_noalloc(const uint8_t* A, const uint8_t* prec, const uin
     if (e != hipSuccess) return fail(COMET_ERR_HIP, "kernel attributes: %s", hipGetErrorString(e));
     g_attr_set[dev] = true;
   }
-  const int kind = kernel_kind(M, N, K, info.cus);
+  std::string mode = sched_mode();
+  const int kind = kernel_kind(M, N, K, info.cus, mode);
   comet::GemmArgs a{};
   a.A = A;
   a.sa = sa;
@@ -515,10 +515,9 @@ comet_status_t run_gemm_noalloc(const uint8_t* A, const uint8_t* prec, const uin
   a.cus = info.cus;
   a.map = map;
   for (int g = 0; g < K / comet::kG; ++g) a.n4 += prec[g] == 4;
-  std::string mode = sched_mode();
-  if (few_token(kind, M, N, K, info.cus, mode)) {
+  if (few_token(kind)) {
     a.splits = comet::skinny_splits(N, K, info.cus);
-    return launched(comet::launch_gemm_skinny(a, false, stream), "gemm launch");
+    return launched(comet::launch_gemm_skinny(a, kind == COMET_KERNEL_PAIR, false, stream), "gemm launch");
   }
   uint8_t* ws = nullptr;
   hipError_t e = comet::noalloc_scratch(dev, &ws);
@@ -843,7 +842,7 @@ int comet_gemm_kernel(int M, int N, int K, int G, int num_cus) {
     return -1;
   }
   if (check_kg(K, G)) return -1;
-  return kernel_kind(M, N, K, num_cus);
+  return kernel_kind(M, N, K, num_cus, sched_mode());
 }
 
 void comet_release_caches(void) {

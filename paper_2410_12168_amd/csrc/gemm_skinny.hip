@@ -724,21 +724,6 @@ const void* pair_kernel(int R, bool diag) {
   return R == 1 ? pair_fn<1>(diag) : R == 2 ? pair_fn<2>(diag) : pair_fn<3>(diag);
 }
 
-// Whether the pair kernel takes this few-token shape: at least two K-blocks a
-// wave, and enough pairs for half of the CUs but no second round of
-// workgroups.  Measured at 256 CUs (us, per-wave or shared kernel -> pairs):
-// K = 28672, 512 panels: M = 16 36.6 -> 27.3, 32 51.7 -> 33.9, 48 65.4 -> 39.3;
-// K = 8192, 512 panels: 13.2 -> 12.3, 17.3 -> 14.3, 21.5 -> 15.0; K = 4096, 384
-// panels: 7.7 -> 7.2, 24 rows 10.1 -> 8.0, 12.4 -> 8.5; K = 14336, 256 panels:
-// 13.8 -> 13.3, 20.0 -> 19.2.  Below 256 panels it loses at 16 rows (8.8 -> 9.7
-// with 234), above 512 too (24 rows, 528 panels: 18.7 -> 20.4), but not at 48
-// rows, where the per-wave kernel is furthest from the weight stream (640
-// panels 27.0 -> 25.0, 1024 39.4 -> 28.4; at 33 rows, 768 panels, 24.4 -> 25.2).
-bool skinny_pair(int M, int N, int K, int cus) {
-  const int P = N / 16;
-  return M > 8 && K / kG >= 2 * kPairWaves && P >= cus && (P <= 2 * cus || M > 40);
-}
-
 constexpr int kPairMaxR = 3;  // row blocks of a row group (four would spill)
 
 // ---------------------------------------------------------------------------
@@ -1478,6 +1463,21 @@ int chunk_lds(int R) {
 
 }  // namespace
 
+// Whether the pair kernel takes this few-token shape: at least two K-blocks a
+// wave, and enough pairs for half of the CUs but no second round of
+// workgroups.  Measured at 256 CUs (us, per-wave or shared kernel -> pairs):
+// K = 28672, 512 panels: M = 16 36.6 -> 27.3, 32 51.7 -> 33.9, 48 65.4 -> 39.3;
+// K = 8192, 512 panels: 13.2 -> 12.3, 17.3 -> 14.3, 21.5 -> 15.0; K = 4096, 384
+// panels: 7.7 -> 7.2, 24 rows 10.1 -> 8.0, 12.4 -> 8.5; K = 14336, 256 panels:
+// 13.8 -> 13.3, 20.0 -> 19.2.  Below 256 panels it loses at 16 rows (8.8 -> 9.7
+// with 234), above 512 too (24 rows, 528 panels: 18.7 -> 20.4), but not at 48
+// rows, where the per-wave kernel is furthest from the weight stream (640
+// panels 27.0 -> 25.0, 1024 39.4 -> 28.4; at 33 rows, 768 panels, 24.4 -> 25.2).
+bool skinny_pair(int M, int N, int K, int cus) {
+  const int P = N / 16;
+  return M > 8 && K / kG >= 2 * kPairWaves && P >= cus && (P <= 2 * cus || M > 40);
+}
+
 bool skinny_stream_eligible(int M, int N, int K, int cus) {
   const int P = N / 16, NG = K / kG;
   if (cus <= 0 || P % cus != 0) return false;
@@ -1512,7 +1512,16 @@ hipError_t set_skinny_attributes() {
   return hipSuccess;
 }
 
-hipError_t launch_gemm_skinny(const GemmArgs& a, bool diag, hipStream_t stream) {
+hipError_t launch_gemm_skinny(const GemmArgs& a, bool pairs, bool diag, hipStream_t stream) {
+  if (pairs) {
+    // row groups of equal height (one up to 48 rows), as row_groups_pay counts them
+    const int rb = (a.M + 15) / 16, ny = (rb + kPairMaxR - 1) / kPairMaxR;
+    const int R = (rb + ny - 1) / ny;
+    GemmArgs args = a;
+    void* params[] = {&args};
+    return hipLaunchKernel(pair_kernel(R, diag), dim3((a.N / 16 + 1) / 2, (rb + R - 1) / R),
+                           dim3(kPairWaves * 64), params, kPairWaves * 2 * R * 64 * 16, stream);
+  }
   if (a.M > 8 && skinny_stream_eligible(a.M, a.N, a.K, a.cus)) {
     const int R = chunk_r(a.M), kp = a.N / 16 / a.cus;
     const void* fn = chunk_kernel(R, diag);
@@ -1543,15 +1552,6 @@ hipError_t launch_gemm_skinny(const GemmArgs& a, bool diag, hipStream_t stream) 
     return hipGetLastError();
   }
 
-  if (a.M > kSkinnyMaxM || skinny_pair(a.M, a.N, a.K, a.cus)) {
-    // row groups of equal height (one up to 48 rows), as row_groups_pay counts them
-    const int rb = (a.M + 15) / 16, ny = (rb + kPairMaxR - 1) / kPairMaxR;
-    const int R = (rb + ny - 1) / ny;
-    GemmArgs args = a;
-    void* params[] = {&args};
-    return hipLaunchKernel(pair_kernel(R, diag), dim3((a.N / 16 + 1) / 2, (rb + R - 1) / R),
-                           dim3(kPairWaves * 64), params, kPairWaves * 2 * R * 64 * 16, stream);
-  }
   if (a.splits < 1 || kWaves % a.splits != 0) return hipErrorInvalidValue;
   // 8 < M <= 32: the shared-activation kernel.  At M <= 8 the per-wave kernel
   // is faster: it needs fewer registers (four waves per SIMD against three),

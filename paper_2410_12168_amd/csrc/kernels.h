@@ -94,13 +94,15 @@ hipError_t launch_swiglu_quantize(const uint16_t* GU, uint8_t* A, uint16_t* sa, 
 // 8 < M <= 64 the K-blocks go in chunks whose activation fragments are staged
 // in LDS.  Otherwise (M <= kSkinnyMaxM) one wave per (16 columns, split-K
 // slot), or, for 8 < M <= 32 with at most two slots, four column blocks per
-// workgroup sharing the activation operand through LDS, or pairs of panels;
-// above kSkinnyMaxM only pairs, in row groups (row_groups_pay).
+// workgroup sharing the activation operand through LDS.  With `pairs`, the pair
+// kernel (any M, K / G >= 1): skinny_pair up to kSkinnyMaxM rows, above them
+// row_groups_pay.
 constexpr int kSkinnyMaxM = 48;
 constexpr int kStreamMaxLds = 160 * 1024;
 bool skinny_stream_eligible(int M, int N, int K, int cus);
+bool skinny_pair(int M, int N, int K, int cus);
 inline bool skinny_shared(int M, int splits) { return M > 8 && M <= 32 && splits <= 2; }
-hipError_t launch_gemm_skinny(const GemmArgs& a, bool diag, hipStream_t stream);
+hipError_t launch_gemm_skinny(const GemmArgs& a, bool pairs, bool diag, hipStream_t stream);
 // Allows the stream kernels' dynamic LDS size; once per process and device.
 hipError_t set_skinny_attributes();
 // Split-K slots (1, 2 or 4) for the few-token kernel: spread the (N/16 x

@@ -1,6 +1,8 @@
 """What the library asks of the HIP runtime, call by call (tests/hip_record.py):
 set-up work is complete before anything can use it.  CPU only.
 """
+import re
+
 import pytest
 
 import hip_record
@@ -56,3 +58,38 @@ print(json.dumps(out))
         assert f"gemm_kernelILi128ELb0ELb0ELb{natural}E" in kernels[0]
     st, kernels, error = out["bogus"]
     assert st == 1 and not kernels and "unknown mode bogus" in error
+
+
+KERNELS = {"skinny": r"skinny_kernelI", "skinny_shared": r"skinny_shared_kernelI",
+           "mid": r"gemm_kernelILi128E", "tile": r"gemm_kernelILi256E",
+           "stream": r"skinny_(chunk|stream)_kernelI", "pair": r"skinny_pair_kernelI"}
+
+
+@pytest.mark.parametrize("mode", ["cost", "dp"])
+def test_the_kernel_that_runs_is_the_one_reported(shim, mode):
+    # every class and both sides of the rules between them; the three entry points
+    # launch what comet_gemm_kernel says
+    body = """
+out = []
+for M in (1, 8, 9, 16, 32, 33, 40, 41, 48, 49, 64, 65, 96, 128, 129, 200, 256, 257, 700, 2000):
+    for N, K in ((1024, 1024), (2048, 896), (4096, 4096), (6144, 4096), (8192, 8192), (9616, 4224),
+                 (10240, 8192), (16384, 2048), (57344, 8192), (57600, 8192)):
+        kind = comet.KERNEL_NAMES[comet.comet_gemm_kernel(M, N, K, 256)]
+        names = []
+        for entry in ("comet_w4ax_gemm", "comet_w4ax_gemm_noalloc"):
+            assert gemm(M, N, K, entry=entry) == 0, comet.comet_last_error()
+            names.append([l.split()[2] for l in log() if l.startswith("launch")][-1])
+        m = bytes([4] * (K // 128))
+        assert comet.lib().comet_w4ax_gemm_acc(P, m, P, P, P, P, M, N, K, 128, 0, 1, 0, 1, 0) == 0
+        names.append([l.split()[2] for l in log() if l.startswith("launch")][-1])
+        out.append([M, N, K, kind, names])
+print(json.dumps(out))
+"""
+    rows = hip_record.run(shim, body, COMET_SCHED=mode)
+    for M, N, K, kind, names in rows:
+        for name in names:
+            assert re.search(KERNELS[kind], name), (M, N, K, kind, name)
+    seen = {(kind, M > 48) for M, _, _, kind, _ in rows}
+    want = {("skinny", False), ("skinny_shared", False), ("stream", False), ("stream", True),
+            ("mid", False), ("mid", True), ("tile", True), ("pair", False)}
+    assert seen == want | ({("pair", True)} if mode == "cost" else set())
