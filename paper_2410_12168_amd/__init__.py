@@ -110,7 +110,17 @@ def _ptr(t):
     return t.data_ptr()
 
 
+# The lookup of the current stream, once the device is initialized (in this
+# process: a forked child starts over, and torch refuses it there).
 _raw_stream = None
+
+
+def _forget_stream():
+    global _raw_stream
+    _raw_stream = None
+
+
+os.register_at_fork(after_in_child=_forget_stream)
 
 
 def _stream(stream):

@@ -313,3 +313,21 @@ def test_unknown_schedule_mode(monkeypatch):
     monkeypatch.setenv("COMET_SCHED", "bogus")
     with pytest.raises(comet.CometError, match="unknown mode"):
         comet.comet_schedule_query(4096, 1024, 1024, [4] * 8)
+
+
+# --- the binding ---------------------------------------------------------------
+
+def test_the_stream_lookup_does_not_outlive_a_fork(monkeypatch):
+    # a child process has no device: its first look at the current stream goes through
+    # torch, which refuses it there, and not to the driver
+    monkeypatch.setattr(comet, "_raw_stream", lambda: 0)
+    r, w = os.pipe()
+    pid = os.fork()
+    if pid == 0:
+        os.write(w, b"%d" % (comet._raw_stream is None))
+        os._exit(0)
+    os.waitpid(pid, 0)
+    assert os.read(r, 8) == b"1"
+    os.close(r)
+    os.close(w)
+    assert comet._raw_stream is not None
