@@ -339,7 +339,13 @@ comet_status_t get_workspace(int dev, hipStream_t stream, size_t partial_floats,
       return fail(COMET_ERR_OOM, "workspace allocation: %s", hipGetErrorString(e));
     }
     e = hipMalloc(&ws.counters, std::max<size_t>(nc, 1) * sizeof(int));
-    if (e == hipSuccess) e = hipMemsetAsync(ws.counters, 0, std::max<size_t>(nc, 1) * sizeof(int), stream);
+    // zero once and for all (every launch leaves them at zero), not as part of a
+    // capture that may be under way on `stream`
+    hipStream_t setup;
+    if (e == hipSuccess) e = setup_stream(dev, &setup);
+    if (e == hipSuccess)
+      e = comet::launch_zero_ints(ws.counters, (int)std::max<size_t>(nc, 1), setup);
+    if (e == hipSuccess) e = hipStreamSynchronize(setup);
     if (e != hipSuccess) {
       (void)hipFree(ws.partials);
       if (ws.counters) (void)hipFree(ws.counters);

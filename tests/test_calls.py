@@ -93,3 +93,19 @@ print(json.dumps(out))
     want = {("skinny", False), ("skinny_shared", False), ("stream", False), ("stream", True),
             ("mid", False), ("mid", True), ("tile", True), ("pair", False)}
     assert seen == want | ({("pair", True)} if mode == "cost" else set())
+
+
+def test_new_counters_are_zero_before_the_launch_that_counts(shim):
+    # a captured call only records what it enqueues on its stream: counters cleared
+    # there would not be zero for an eager call, and a memset in a graph is not
+    # reliable on replays
+    log = hip_record.run(shim, """
+assert gemm(700, 1024, 1024, stream=0x1000) == 0, comet.comet_last_error()
+print(json.dumps(log()))
+""")
+    assert not any(l.startswith("memset") for l in log)
+    zero = next(i for i, l in enumerate(log) if l.startswith("launch") and "zero_ints" in l)
+    stream = log[zero].split()[1]
+    assert stream != str(0x1000)
+    gemm = next(i for i, l in enumerate(log) if l.startswith(f"launch {0x1000} "))
+    assert f"synchronize {stream}" in log[zero:gemm]
