@@ -1464,18 +1464,28 @@ int chunk_lds(int R) {
 }  // namespace
 
 // Whether the pair kernel takes this few-token shape: at least two K-blocks a
-// wave, and enough pairs for half of the CUs but no second round of
-// workgroups.  Measured at 256 CUs (us, per-wave or shared kernel -> pairs):
-// K = 28672, 512 panels: M = 16 36.6 -> 27.3, 32 51.7 -> 33.9, 48 65.4 -> 39.3;
-// K = 8192, 512 panels: 13.2 -> 12.3, 17.3 -> 14.3, 21.5 -> 15.0; K = 4096, 384
-// panels: 7.7 -> 7.2, 24 rows 10.1 -> 8.0, 12.4 -> 8.5; K = 14336, 256 panels:
-// 13.8 -> 13.3, 20.0 -> 19.2.  Below 256 panels it loses at 16 rows (8.8 -> 9.7
-// with 234), above 512 too (24 rows, 528 panels: 18.7 -> 20.4), but not at 48
-// rows, where the per-wave kernel is furthest from the weight stream (640
-// panels 27.0 -> 25.0, 1024 39.4 -> 28.4; at 33 rows, 768 panels, 24.4 -> 25.2).
+// wave, enough pairs for half of the CUs and, up to two row blocks, no second
+// round of workgroups.  Measured at 256 CUs, rotated weights (us, per-wave or
+// shared kernel -> pairs), up to 512 panels:
+//   K = 28672, 512 panels: 16 / 32 / 48 rows 36.6 -> 27.3, 51.7 -> 33.9, 65.4 -> 39.3
+//   K =  8192, 512 panels: the same rows 13.2 -> 12.3, 17.3 -> 14.3, 21.5 -> 15.0
+//   K =  4096, 384 panels: 16 / 24 / 48 rows 7.7 -> 7.2, 10.1 -> 8.0, 12.4 -> 8.5
+//   K = 14336, 256 panels: 13.8 -> 13.3 at 16 rows, 20.0 -> 19.2 at 48
+//   K =  4096, 234 panels: 8.8 -> 9.7 at 16 rows (too few pairs)
+// and above 512 panels, where a second round lies half empty; the per-wave
+// kernel pays for its third row block what the pair kernel loses by that:
+//   K = 8192,  520 panels: 9 / 24 / 32 / 33 / 40 / 48 rows
+//                          13.6 -> 17.8, 19.1 -> 20.9, 20.5 -> 21.3, 23.9 -> 23.0, 25.3 -> 23.6, 26.7 -> 23.9
+//   K = 8192,  768 panels: 32 / 33 / 36 / 40 / 48 rows
+//                          21.2 -> 23.7, 24.9 -> 25.1, 25.3 -> 25.3, 25.9 -> 25.6, 27.5 -> 26.2
+//   K = 8192, 1000 panels: 32 / 33 / 48 rows 25.2 -> 26.1, 38.9 -> 27.6, 39.1 -> 28.7
+//   K = 8192, 1600 panels: the same rows 42.2 -> 45.1, 49.4 -> 47.9, 55.9 -> 49.7
+//   K = 4096,  640 panels: the same rows 13.0 -> 14.1, 15.2 -> 14.8, 16.6 -> 15.2
+//   K = 8192, 2500 panels: 33 / 48 rows 66.6 -> 63.1, 75.6 -> 65.8; half of the
+//                          K-blocks 8-bit 80.4 -> 71.2, 96.9 -> 77.7
 bool skinny_pair(int M, int N, int K, int cus) {
   const int P = N / 16;
-  return M > 8 && K / kG >= 2 * kPairWaves && P >= cus && (P <= 2 * cus || M > 40);
+  return M > 8 && K / kG >= 2 * kPairWaves && P >= cus && (P <= 2 * cus || M > 32);
 }
 
 bool skinny_stream_eligible(int M, int N, int K, int cus) {

@@ -257,10 +257,10 @@ def test_gemm_kernel_choice(monkeypatch):
     assert [k(m, 57344, 8192, 256) for m in (1, 8, 16, 32, 33, 48, 64, 65, 128, 129, 4096)] == \
         [4, 4, 4, 4, 4, 4, 4, 2, 2, 3, 3]
     # panels that do not divide over the CUs (304): few-token kernels up to 48
-    # rows (224 column tiles are too few for 304 CUs; pairs of panels above 40
+    # rows (224 column tiles are too few for 304 CUs; pairs of panels above 32
     # rows), 128-row tiles up to 128
     assert [k(m, 57344, 8192, 304) for m in (1, 8, 16, 32, 33, 48, 64, 128, 129, 4096)] == \
-        [0, 0, 1, 1, 0, 5, 2, 2, 3, 3]
+        [0, 0, 1, 1, 5, 5, 2, 2, 3, 3]
     # one panel per CU: too few items for either stream kernel; pairs of panels
     # above 8 rows, in row groups above 48
     assert [k(m, 4096, 8192, 256) for m in (8, 9, 33, 48, 49)] == [0, 5, 5, 5, 5]
