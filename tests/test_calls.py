@@ -109,3 +109,22 @@ print(json.dumps(log()))
     assert stream != str(0x1000)
     gemm = next(i for i, l in enumerate(log) if l.startswith(f"launch {0x1000} "))
     assert f"synchronize {stream}" in log[zero:gemm]
+
+
+def test_swiglu_is_fused_exactly_where_the_128_row_kernel_runs(shim):
+    rows = hip_record.run(shim, """
+out = []
+for M, N, K in ((8, 512, 1024), (100, 768, 1024), (100, 768, 640), (100, 33280, 1024), (300, 1024, 2048),
+                (1024, 20480, 1024), (128, 57344, 8192)):
+    kind = comet.KERNEL_NAMES[comet.comet_gemm_kernel(M, N, K, 256)]
+    assert swiglu(M, N, K, stream=0x1000) == 0, comet.comet_last_error()
+    names = [l.split()[2] for l in log() if l.startswith(f"launch {0x1000} ")]
+    out.append([kind, names])
+print(json.dumps(out))
+""")
+    for kind, names in rows:
+        assert re.search(KERNELS[kind], names[0]), (kind, names)
+        fused = "gemm_kernelILi128ELb0ELb1E" in names[0]
+        assert fused == (kind == "mid")
+        assert len(names) == (1 if fused else 2)
+    assert {kind for kind, _ in rows} == {"skinny", "pair", "mid", "tile"}

@@ -232,16 +232,20 @@ def gemm_inputs(M, N, K, seed):
     return prec, A, sa, Wp, sw
 
 
-# few-token (two-step), 128-row tiles, 256-row tiles, split tiles (320 tiles)
-FUSED = [(8, 512, 1024), (100, 768, 1024), (300, 1024, 2048), (1024, 20480, 1024)]
+# few-token and row groups (two-step), 128-row tiles (fused; cut into three slots,
+# and three and eight), 256-row tiles (two-step; split, 320 tiles)
+FUSED = [(8, 512, 1024, "skinny"), (100, 768, 1024, "pair"), (100, 768, 640, "mid"),
+         (49, 33280, 1024, "mid"), (300, 1024, 2048, "mid"), (1024, 20480, 1024, "tile")]
 
 
-@pytest.mark.parametrize("M,N,K", FUSED)
-def test_fused_swiglu_matches_oracle_on_gemm_output(M, N, K):
+@pytest.mark.parametrize("M,N,K,kernel", FUSED)
+def test_fused_swiglu_matches_oracle_on_gemm_output(M, N, K, kernel):
     """The fused epilogue's quantized h is bit-identical to the oracle's SwiGLU
     quantization of the same GEMM's fp16 output (the plain entry point, same
     schedule, so the same fp16 gate/up values)."""
     print(f"fused swiglu M={M} N={N} K={K}", flush=True)
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert comet.KERNEL_NAMES[comet.comet_gemm_kernel(M, N, K, 256)] == kernel
     I = N // 2
     prec, A, sa, Wp, sw = gemm_inputs(M, N, K, seed=M + N)
     out_map = synth.prec_map(I // 128, max(1, I // 128 // 4), "random", seed=N)

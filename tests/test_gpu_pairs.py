@@ -1,7 +1,9 @@
 """The pair kernel of the few-token GEMM (8 < M <= 48, two weight panels per
 workgroup, K split over its sixteen waves): row-block edges, an odd panel count,
 uneven slots and 8-bit blocks, against the CPU oracle; exact block sums of a
-window; and the same bits on a second call.  Then its row groups (48 < M <= 256).
+window; and the same bits on a second call.  With more than two panels per CU it
+runs from 33 rows on, below them the per-wave kernel.  Then its row groups
+(48 < M <= 256).
 """
 import numpy as np
 import pytest
@@ -11,7 +13,7 @@ import oracle
 import paper_2410_12168_amd as comet
 import synth
 from parity import assert_out_close
-from test_gpu_parity import dev_u16, host, host_u16
+from test_gpu_parity import assert_kernel, dev_u16, host, host_u16
 
 pytestmark = pytest.mark.gpu
 
@@ -22,6 +24,7 @@ def test_pair_kernel(M, panels, NG, n8):
     N, K = 16 * panels, 128 * NG
     prec = synth.prec_map(NG, n8, "random", seed=M)
     print(f"M={M} N={N} K={K} n8={n8}", flush=True)
+    assert_kernel("pair" if panels <= 512 or M > 32 else "skinny", M, N, K)
     x16, w16 = synth.activations(M, M, K, prec), synth.weights(panels, N, K)
     A, sa = comet.quantize_act(dev_u16(x16), prec)
     Wp, sw = comet.pack_w4(dev_u16(w16))
@@ -41,6 +44,7 @@ def test_row_groups(M, panels, NG, n8):
     # more than 48 rows of a shape with too few tiles: groups of 32 or 48 rows, the
     # last one ragged, one panel or an odd count, fewer K-blocks than waves
     N, K = 16 * panels, 128 * NG
+    assert_kernel("pair", M, N, K)
     prec = synth.prec_map(NG, n8, "random", seed=M)
     print(f"M={M} N={N} K={K} n8={n8}", flush=True)
     x16, w16 = synth.activations(M, M, K, prec), synth.weights(panels, N, K)

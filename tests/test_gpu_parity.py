@@ -44,19 +44,33 @@ def run_path(M, N, K, prec, seed, diag_window=None):
     return res
 
 
+def assert_kernel(name, M, N, K):
+    """The shape runs the kernel a test means (on 256 compute units)."""
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert comet.KERNEL_NAMES[comet.comet_gemm_kernel(M, N, K, 256)] == name, (M, N, K)
+
+
 SHAPES = [
     # (M, N, K, map kind) -- several tiles, ragged tails, both precisions
     (16, 1024, 1024, "cfg0"),
     (1, 16, 128, "all4"),
     (3, 48, 256, "all8"),
-    (100, 272, 1152, "random"),
     (257, 400, 640, "alternate"),
     (130, 144, 384, "cfg0"),
-    # 128-row tiles (64 < M <= 128): ragged rows and columns, both precisions
-    (65, 528, 640, "alternate"),
+    # the pair kernel's row groups (up to 256 rows, eight K-blocks or more)
+    (100, 272, 1152, "random"),
     (128, 784, 1024, "all8"),
     (97, 4096, 2048, "random"),
+    # 128-row tiles: ragged rows and columns, both precisions, split tiles
+    (65, 528, 640, "alternate"),
+    (120, 784, 896, "all8"),
+    (49, 33296, 1024, "random"),
+    (300, 400, 1024, "alternate"),
 ]
+KERNELS = {(16, 1024, 1024): "skinny_shared", (257, 400, 640): "tile", (130, 144, 384): "tile",
+           (100, 272, 1152): "pair", (128, 784, 1024): "pair", (97, 4096, 2048): "pair",
+           (65, 528, 640): "mid", (120, 784, 896): "mid", (49, 33296, 1024): "mid",
+           (300, 400, 1024): "mid"}
 
 
 def make_map(kind, NG, seed):
@@ -85,6 +99,8 @@ def test_quantize_and_pack_bit_exact(M, N, K, kind):
 
 @pytest.mark.parametrize("M,N,K,kind", SHAPES)
 def test_gemm_matches_oracle(M, N, K, kind):
+    if (M, N, K) in KERNELS:
+        assert_kernel(KERNELS[M, N, K], M, N, K)
     prec = make_map(kind, K // 128, seed=M)
     win = (0, min(M, 37), max(0, N - 40), N)
     r = run_path(M, N, K, prec, seed=M + N, diag_window=win)
@@ -96,8 +112,11 @@ def test_gemm_matches_oracle(M, N, K, kind):
     assert_out_close(host_u16(r["out"]).view(np.float16), ref, f"{M}x{N}x{K}/{kind}")
 
 
-def test_gemm_run_twice_bit_identical():
-    M, N, K = 130, 400, 1024
+@pytest.mark.parametrize("M,N,K,kernel", [(130, 400, 1024, "pair"), (300, 400, 1024, "mid"),
+                                          (257, 400, 640, "tile")])
+def test_gemm_run_twice_bit_identical(M, N, K, kernel):
+    # the tiles of the last two are cut into four and three slots
+    assert_kernel(kernel, M, N, K)
     prec = synth.prec_map(K // 128, 2, "random", 4)
     r = run_path(M, N, K, prec, seed=11)
     again = comet.w4ax_gemm(r["A"], prec, r["sa"], r["Wp"], r["sw"], M, N, K)

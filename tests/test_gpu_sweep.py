@@ -8,11 +8,14 @@ three-row-block few-token (32 < M <= 48), 128-row (48 < M <= 128) and
 256-row tile (M > 128, up to several row tiles) kernels, with ragged M, N
 and K, small column counts that make the tile kernels split every tile over
 many workgroups, and all the precision-map kinds.  The oracle's cost bounds the sizes.
+So small, most shapes of 49 to 256 rows run the pair kernel's row groups; they run
+once more on the tile kernels, in the schedule modes that leave tiles whole.
 """
 import numpy as np
 import pytest
 
 import oracle
+import paper_2410_12168_amd as comet
 from parity import assert_out_close
 from test_gpu_parity import host, host_u16, make_map, run_path
 
@@ -38,6 +41,14 @@ def sweep_shapes(n_per_regime=6, seed=20241016, budget=2.5e8):
 
 
 SHAPES = sweep_shapes()
+
+
+@pytest.mark.parametrize("mode", ["dp", "natural"])
+@pytest.mark.parametrize("M,N,K,kind", [s for s in SHAPES if 48 < s[0] <= 256])
+def test_sweep_on_whole_tiles(monkeypatch, M, N, K, kind, mode):
+    monkeypatch.setenv("COMET_SCHED", mode)
+    assert comet.KERNEL_NAMES[comet.comet_gemm_kernel(M, N, K, 256)] in ("mid", "tile")
+    test_sweep_matches_oracle(M, N, K, kind)
 
 
 @pytest.mark.parametrize("M,N,K,kind", SHAPES)

@@ -15,7 +15,7 @@ import oracle
 import paper_2410_12168_amd as comet
 import synth
 from parity import act_rows, assert_out_close
-from test_gpu_parity import DEV, dev_u16, host, host_u16, run_path
+from test_gpu_parity import DEV, assert_kernel, dev_u16, host, host_u16, run_path
 
 pytestmark = pytest.mark.gpu
 
@@ -77,20 +77,23 @@ def test_split_tile_acc_window_production_plan():
     assert_out_close(out, ref, "split tile window")
 
 
-@pytest.mark.parametrize("M,N,K", [(512, 8192, 8192), (2048, 4096, 14336)])
-def test_split_tiles_sum_in_slot_order(M, N, K):
-    """Plans whose tiles are split: 512 x 8192 x 8192 cuts each of its 64
-    tiles into four slots (all partials added in slot order); the 8B down
-    projection's 128 tiles into two (the finishing slot adds the other's
-    partial to its registers).  The fp16 output must match the oracle and be
-    bit-identical from run to run, whichever slot arrives last."""
+@pytest.mark.parametrize("M,N,K,slots,tile_m", [
+    (512, 8192, 8192, 2, 128), (2048, 4096, 14336, 2, 256),
+    (300, 1024, 2048, 8, 128), (257, 400, 640, 3, 256)])
+def test_split_tiles_sum_in_slot_order(M, N, K, slots, tile_m):
+    """Plans whose tiles are split, of both heights: into two slots (the
+    finishing slot adds the other's partial to its registers), and into three
+    and eight (all partials added in slot order).  The fp16 output must match
+    the oracle and be bit-identical from run to run, whichever slot arrives
+    last."""
     NG = K // 128
     prec = synth.prec_map(NG, NG // 16, "random", seed=M)
     cus = torch.cuda.get_device_properties(0).multi_processor_count
     q = comet.comet_schedule_query(M, N, K, prec, num_cus=cus)
     nslots = q["units"][:, 4].max()
     print(f"split slots M={M} N={N} K={K}: up to {nslots} slots per tile", flush=True)
-    assert nslots >= 2
+    assert (nslots, q["tile_m"]) == (slots, tile_m) or cus != 256
+    assert_kernel("mid" if tile_m == 128 else "tile", M, N, K)
     r = run_path(M, N, K, prec, seed=41)
     rows = tile_rows(M, tile=q["tile_m"], seed=3)
     qa, sa = oracle.quantize_act(r["X16"][rows], prec)
@@ -180,11 +183,13 @@ def test_fused_swiglu_wide_n_mid_rows(N, kind):
 
 @pytest.mark.parametrize("M,N,K,placement", [(4096, 10240, 8192, "random"),
                                              (300, 1024, 4096, "contiguous"),
-                                             (100, 2048, 2048, "random")])
+                                             (100, 2048, 2048, "random"),
+                                             (49, 33296, 1024, "random")])
 def test_schedule_modes_agree(M, N, K, placement):
     """natural (map order, whole tiles), dp (precision-batched, whole tiles)
-    and cost (precision-batched, split last wave) give bit-identical block
-    sums and outputs within the oracle tolerance."""
+    and cost (precision-batched, split last wave; 100 x 2048 x 2048: the pair
+    kernel) give bit-identical block sums and outputs within the oracle
+    tolerance."""
     NG = K // 128
     prec = synth.prec_map(NG, NG // 4, placement, seed=K)
     X16 = synth.activations(7, M, K, prec)
@@ -202,6 +207,8 @@ def test_schedule_modes_agree(M, N, K, placement):
         for mode in ("natural", "dp", "cost"):
             print(f"schedule mode {mode} M={M} N={N} K={K}", flush=True)
             os.environ["COMET_SCHED"] = mode
+            assert_kernel("pair" if mode == "cost" and M == 100 else "mid" if M < 4096 else "tile",
+                          M, N, K)
             out = comet.w4ax_gemm(A, prec, sa, Wp, sw, M, N, K)
             acc = comet.w4ax_gemm_acc(A, prec, sa, Wp, sw, M, N, K, *win)
             assert np.array_equal(host(acc), acc_ref), mode

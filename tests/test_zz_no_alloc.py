@@ -54,8 +54,10 @@ CASES = [
     ((4096, 10240, 8192), (300, 1024, 2048)),
     # LLaMA-3-8B o projection (128 tiles, all split), then a smaller split plan
     ((2048, 4096, 4096), (1024, 2048, 1024)),
-    # 128-row tiles (70B gate_up at M = 128), then a ragged one
+    # 128-row tiles (70B gate_up at M = 128), then a ragged one of row groups (no
+    # workspace), and two split ones
     ((128, 57344, 8192), (65, 512, 1024)),
+    ((49, 33296, 1024), (300, 400, 1024)),
     # few-token kernels (no workspace)
     ((8, 8192, 4096), (1, 256, 1024)),
 ]
@@ -82,18 +84,20 @@ def test_noalloc_allocates_nothing():
     memory unchanged."""
     print("noalloc free memory", flush=True)
     o1, o2 = operands(2048, 4096, 4096, seed=3), operands(128, 8192, 2048, seed=4)
-    o3 = operands(8, 1024, 1024, seed=5)
-    outs = [torch.empty((o["M"], o["N"]), dtype=torch.float16, device=DEV) for o in (o1, o2, o3)]
-    for o, out in zip((o1, o2, o3), outs):
+    o3, o4 = operands(8, 1024, 1024, seed=5), operands(300, 1024, 2048, seed=6)
+    calls = (o1, o2, o3, o4)  # 128-row tiles, row groups, few tokens, split 128-row tiles
+    outs = [torch.empty((o["M"], o["N"]), dtype=torch.float16, device=DEV) for o in calls]
+    for o, out in zip(calls, outs):
         noalloc(o, out)
     torch.cuda.synchronize()
     free0 = torch.cuda.mem_get_info()[0]
     for _ in range(3):
-        for o, out in zip((o1, o2, o3), outs):
+        for o, out in zip(calls, outs):
             noalloc(o, out)
     torch.cuda.synchronize()
     assert torch.cuda.mem_get_info()[0] == free0
     check(o1, outs[0])
+    check(o4, outs[3])
 
 
 def test_noalloc_refuses_oversized_schedule():
