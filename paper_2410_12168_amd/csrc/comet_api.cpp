@@ -231,9 +231,7 @@ comet::PlanOptions plan_options(int M, int N, int K, int cus, const std::string&
 
 // A plan as the kernels read it, one int array: work units (5 ints each) |
 // wg_begin | K-block schedule (block index, precision bit and the block's
-// offset in A_packed in units of M*64 bytes, then kOrderPad repeats of the
-// last entry, since kernels prefetch fixed-size batches past the end of a
-// range) | split table.
+// offset in A_packed in units of M*64 bytes) | split table.
 struct PlanBlob {
   std::vector<int> v;
   size_t o_wgb = 0, o_order = 0, o_split = 0;
@@ -254,8 +252,6 @@ PlanBlob plan_blob(const comet::Plan& h, const uint8_t* prec) {
   std::vector<int> n8_before(h.order.size() + 1, 0);
   for (size_t g = 0; g < h.order.size(); ++g) n8_before[g + 1] = n8_before[g] + (prec[g] == 8);
   for (int g : h.order) b.v.push_back(g | (prec[g] == 8) << 10 | (g + n8_before[g]) << 11);
-  const int last = b.v.back();
-  b.v.insert(b.v.end(), comet::kOrderPad, last);
   b.o_split = b.v.size();
   b.v.insert(b.v.end(), h.split_base.begin(), h.split_base.end());
   return b;

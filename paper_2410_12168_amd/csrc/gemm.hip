@@ -113,9 +113,10 @@ __device__ __forceinline__ int rpos(int r, int j) { return r * 64 + ((j ^ ((r >>
 // A 4-bit block's activation codes in a stage: FP8 bytes in fragment order.
 // The 1 KB unit ((rb * 2 + h) * 2 + p) holds, for row block rb and K-half h
 // (codes 64 h .. 64 h + 63), 16 bytes per lane: lane l's are codes 64 h + 32
-// (l / 32) + 16 p .. + 15 of row 32 rb + l % 32, in place l ^ 2 (l / 32), K-half 1 64 bytes
-// further on.  That spreads the writes of the unpacked codes, whose lanes hold the
-// four chunks of two rows in eight lanes, over all banks, and leaves the reads spread.
+// (l / 32) + 16 p .. + 15 of row 32 rb + l % 32, in place l ^ 2 (l / 32), K-half 1
+// 64 bytes further on.  That spreads the writes of the unpacked codes, whose lanes
+// hold the four chunks of two rows in eight lanes, over all banks, and leaves the
+// reads spread.
 __device__ __forceinline__ constexpr int aunit(int rb, int h, int p) {
   return rb * kARb + h * (2048 + 64) + p * 1024;
 }
@@ -393,9 +394,9 @@ __device__ __forceinline__ i32x8 unpack_frag(u32x4 v) {
 __device__ __forceinline__ void order_point() { __builtin_amdgcn_sched_barrier(0); }
 
 // Accumulators of a wave's quadrant, in units of 2^-17 (the FP8 code
-// encoding, and P = 2 sa sw, see scale_products32), and the block whose dequantization is still due, the last one of
-// the K-block before: C[NB - 1] += y * P.  Block b is row block b / CB, column
-// block b % CB.
+// encoding, and P = 2 sa sw, see scale_products32), and the block whose
+// dequantization is still due, the last one of the K-block before:
+// C[NB - 1] += y * P.  Block b is row block b / CB, column block b % CB.
 template <int TM>
 struct Acc {
   static constexpr int NB = Geo<TM>::NB;
@@ -672,10 +673,11 @@ __device__ __forceinline__ void kloop_phases(const GemmArgs& p, uint8_t* smem, u
 
 // K-loop as kloop_phases, of precision B8, with all waves in step and one barrier
 // per K-block: for the 128-row tile, and for 8-bit blocks, whose longer chains of
-// MFMAs and dequantizations the SIMD's two waves fill better side by side.  In iteration j waves 0-3 (LEAD false) unpack the
-// activation codes of j + 1, after computing, into the stage that j - 1 left
-// free, and start the loads of j + 2; waves 4-7 load weights j + D - 1 into the
-// ring slot of j - 1 and wait, at the end, for j + 1.
+// MFMAs and dequantizations the SIMD's two waves fill better side by side.  In
+// iteration j waves 0-3 (LEAD false) unpack the activation codes of j + 1, after
+// computing, into the stage that j - 1 left free, and start the loads of j + 2;
+// waves 4-7 load weights j + D - 1 into the ring slot of j - 1 and wait, at the
+// end, for j + 1.
 template <int TM, bool DIAG, bool B8, bool LEAD>
 __device__ __forceinline__ void kloop_step(const GemmArgs& p, uint8_t* smem, uint32_t lds,
                                             const int* order, int g_begin, int pos, int end,
@@ -897,7 +899,8 @@ __device__ __forceinline__ void store_tile(const GemmArgs& p, const WorkUnit& un
         for (int q = 0; q < 4; ++q)
           *reinterpret_cast<f32x4*>(part + (((wave * L::NB + b) * 4 + q) * 64 + lane) * 4) =
               f32x4{C[b][4 * q], C[b][4 * q + 1], C[b][4 * q + 2], C[b][4 * q + 3]};
-      // the barrier completes every wave's partial stores into L2
+      // the barrier orders every wave's partial stores before the first thread's
+      // device-scope release below
       __syncthreads();
       if (threadIdx.x == 0) {
         __threadfence();

@@ -543,16 +543,21 @@ hipError_t launch_shared(const GemmArgs& a, bool diag, hipStream_t stream) {
 
 
 // ---------------------------------------------------------------------------
-// Few-token kernel over pairs of panels (M > 8, long K).  The per-wave
+// Few-token kernel over pairs of panels (M > 8; 32 K-blocks or more up to 48 rows,
+// see skinny_pair, and 8 or more in row groups, where some of the sixteen waves may
+// have none).  The per-wave
 // kernel above gives every wave one panel, so each K-block's activation codes
 // (1 KB per row block) are read and unpacked for one kilobyte of weights; at
 // three row blocks that, not the weight stream, is its time, and with one or
 // two slots a SIMD has one wave to hide it behind.  Here a workgroup of 16
 // waves owns two panels and its waves split K sixteen ways: a wave's activation
-// fragments serve both panels, four waves share a SIMD, and a wave's weights
-// (three K-blocks in flight) are still one contiguous run per panel.  The
-// partial sums are added in slot order through LDS (deterministic, no
-// cross-workgroup traffic).
+// fragments serve both panels, four waves share a SIMD, and a wave's weights are
+// still one contiguous run per panel, requested three K-blocks ahead (two with
+// three row blocks: registers).  What bounds it: vector loads complete in order,
+// and a step issues its activation loads behind the weights of the step before, so
+// its wait for them is one for those weights too, whatever the depth; a K-block of
+// a wave takes 2.3 to 2.65 us (see row_groups_pay).  The partial sums are added in
+// slot order through LDS (deterministic, no cross-workgroup traffic).
 // More rows go in groups of up to 48 (blockIdx.y) where row_groups_pay says so:
 // with few weight panels the 128- and 256-row tiles are too few for the CUs, and
 // the partial tiles they are cut into cost more than reading weights and

@@ -9,7 +9,6 @@ namespace comet {
 
 constexpr int kG = 128;          // block size along K (the paper's k = 128)
 constexpr int kMaxBlocks = 512;  // blocks per row supported by the bit map (K <= 65536)
-constexpr int kOrderPad = 16;    // entries after the K-block order that repeat its last entry
 
 // Precision of every K-block as a bit set (bit g = 1: block g is 8-bit),
 // passed by value as a kernel argument so no device table is needed.
@@ -38,7 +37,7 @@ struct GemmArgs {
   int* counters;      // per split tile arrival counters (zero between launches)
   const WorkUnit* units;
   const int* wg_begin;
-  const int* order;   // K-block schedule, K/G (+ kOrderPad) entries: g | is8 << 10 | (g + 8-bit blocks before g) << 11
+  const int* order;   // K-block schedule, K/G entries: g | is8 << 10 | (g + 8-bit blocks before g) << 11
   int n4;             // number of 4-bit blocks (they come first in `order`, except in natural order)
   const int* split_index;  // tile -> index into the partial/counter arrays (-1: not split)
   int M, N, K;

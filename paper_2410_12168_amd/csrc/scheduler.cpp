@@ -272,7 +272,16 @@ int skinny_splits(int N, int K, int cus) {
 // groups): 4096 x 4096 at 64 / 128 / 256 rows 38.5 -> 7.8, 39.5 -> 14.3,
 // 34.8 -> 20.7; K = 14336, N = 4096 at 64 rows 46.3 -> 16.1; 8192 x 8192 at 64 /
 // 96 rows 40.0 -> 25.4, 39.7 -> 28.3, but at 128 rows with half of the blocks
-// 8-bit 43.3 -> 45.9.  More than 256 rows were not measured in full.
+// 8-bit 43.3 -> 45.9.  With SwiGLU the pairs need the standalone quantizer behind
+// them (3.5 to 4.2 us), and the fused epilogue costs the tiles about 8 us, so the
+// same rule holds: ten layers at 49 to 128 rows, fused -> pairs and quantizer,
+// 0.26 to 0.81 of the time (K = 3072, N = 16384 at 96 rows, half of the blocks
+// 8-bit, 44.3 -> 35.8).
+// The cap at 256 rows is how far the groups were built and tested, not where they
+// stop winning on the smallest layers: 2048 x 2048 at 320 / 384 / 512 rows takes
+// 36.7 / 36.9 / 32.1 us in tiles, 9.6 / 9.8 / 13.4 in groups, 4096 x 4096 37.5 /
+// 37.2 / 36.4 and 26.1 / 26.4 / 37.7; from K = 14336, N = 4096 (54.6 -> 67.6 at 320
+// rows) and 8192 x 8192 (58.7 -> 87.2) up the tiles win there.
 bool row_groups_pay(int M, int N, int K, int G, int cus) {
   if (cus <= 0 || M > 256 || K / G < 8) return false;
   const int rb = (M + 15) / 16, ny = (rb + 2) / 3, R = (rb + ny - 1) / ny;
