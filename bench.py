@@ -159,7 +159,8 @@ def parse():
     ap.add_argument("--placement", default="contiguous", choices=["contiguous", "random"],
                     help="where the 8-bit blocks sit (a contiguous run, or a seeded random subset)")
     ap.add_argument("--layers", default="",
-                    help="comma-separated subset of the workload's layers (default: all)")
+                    help="comma-separated subset of the model's layers (default: the "
+                         "workload's)")
     ap.add_argument("--copy-mib", type=int, default=0,
                     help="after timing, run one device-to-device copy of this many MiB (a "
                          "known-size reference for HBM byte counters)")
@@ -200,7 +201,7 @@ def main():
         return bench_mlp(args, wl, dev)
     M = args.m or wl["M"]
     shapes = getattr(synth, wl["layers"])
-    if "only" in wl:
+    if "only" in wl and not args.layers:
         shapes = {wl["only"]: shapes[wl["only"]]}
     rotate = wl.get("rotate", 1)
     layers = []
