@@ -54,7 +54,10 @@
  *       COMET_ERR_OOM         : the library could not allocate its workspace.
  *   - Faults inside kernels surface at the caller's next synchronisation.
  *   - Calls on different streams may run concurrently.  The GEMM's split-tile
- *     workspace is owned by the library, one per device and stream.
+ *     workspace is owned by the library, one per device and stream.  It grows
+ *     (and moves) with the largest call on its stream, so a captured call may be
+ *     replayed until a larger one on that stream or comet_release_caches()
+ *     replaces it; comet_w4ax_gemm_noalloc has no such limit.
  *   - The 128- and 256-row tile kernels run from a schedule (plan) that the
  *     library builds on the host and uploads on the first call for each
  *     (device, M, N, K, map, mode): that call allocates a few KB of device

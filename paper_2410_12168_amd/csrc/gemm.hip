@@ -22,9 +22,11 @@
 // dequantization measured 45 cycles at best (54 as the compiler orders them)
 // for 32 of matrix work; a 32x32x64 reads half the operand registers per
 // product, and with P on the matrix core the same work takes 43, 40 of them
-// matrix work, if no wait falls between (register-only, 2.4 GHz).  The kernels
-// reach 60 to 65: the rest is the LDS traffic (fragments, unpacking, direct
-// loads) and the barriers.
+// matrix work, if no wait falls between (register-only, 2.4 GHz).  The 256-row
+// tile reaches 67: one of the two pipes is busy 88% of the time, the rest is LDS
+// traffic (fragments, unpacking, direct loads) and barriers.  The 128-row tile is at
+// 89, with both pipes idle nearly half of the time: four MFMA blocks a wave between
+// barriers are too few to cover the fragment reads and waves 0-3's unpacking.
 //
 // Kernel structure (the gfx950 form of the paper's software pipeline,
 // Sec. 4.2, and of its tile decomposition, Sec. 4.4):
@@ -41,13 +43,15 @@
 //   * split tiles write fp32 partials; the last workgroup to finish a tile
 //     (arrival counter, no waiting) adds the partials in slot order and
 //     stores fp16, so the result does not depend on arrival order.
-// Measured (LLaMA-3-70B, 1/16 of the blocks 8-bit, back to back, against
-// 16x16x128 MFMAs with P on the vector ALU and one barrier per K-block for both
-// tiles): gate_up at 4096 tokens 1895 -> 1783 us, qkv 351 -> 317 us; gate_up at
-// 128 tokens 88.3 -> 84.5 us; LLaMA-3-8B o at 1900 tokens 47.8 -> 44.9 us.  One
-// scale operand per column block (scale_products32) in place of both side by
-// side took gate_up with its quantizer from 1767 to 1728 us at 4096 tokens and
-// from 86.0 to 82.6 us at 128.
+// Measured (LLaMA-3-70B, 1/16 of the blocks 8-bit): gate_up at 4096 tokens 1696 us,
+// qkv 324 us; gate_up at 128 tokens 80 to 84 us; LLaMA-3-8B o at 2048 tokens 44 us.
+// Steps on the way, each against its predecessor on one box, back to back:
+// 32x32x64 MFMAs with P on the matrix core and phases, against 16x16x128 MFMAs with
+// P on the vector ALU and one barrier per K-block for both tiles, gate_up 1895 ->
+// 1783 us at 4096 tokens and 88.3 -> 84.5 us at 128, qkv 351 -> 317 us; one scale
+// operand per column block (scale_products32) in place of both side by side, gate_up
+// with its quantizer 1767 -> 1728 and 86.0 -> 82.6 us; one write of M0 for a wave's
+// four weight panels (dma16_from4) in place of four, 1731 -> 1723 and 85.9 -> 81.3 us.
 #include <hip/hip_runtime.h>
 #include <hip/hip_fp16.h>
 #include <stdint.h>
