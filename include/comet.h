@@ -57,7 +57,7 @@
  *     workspace is owned by the library, one per device and stream.  It grows
  *     (and moves) with the largest call on its stream, so a captured call may be
  *     replayed until a larger one on that stream or comet_release_caches()
- *     replaces it; comet_w4ax_gemm_noalloc has no such limit.
+ *     replaces it.
  *   - The 128- and 256-row tile kernels run from a schedule (plan) that the
  *     library builds on the host and uploads on the first call for each
  *     (device, M, N, K, map, mode): that call allocates a few KB of device
@@ -234,7 +234,10 @@ COMET_API comet_status_t comet_w4ax_gemm(const uint8_t* A_packed, const uint8_t*
  *     output tiles) is refused with COMET_ERR_UNSUPPORTED;
  *   - the first call after the schedule changes (a new shape, map or mode)
  *     copies the schedule from host memory and waits for the copy; calls that
- *     repeat the previous shape only enqueue kernels. */
+ *     repeat the previous shape only enqueue kernels.  A captured call reads the
+ *     schedule that the array holds when it is replayed: replay it only while no
+ *     call of another shape, map or mode has come in between (the kernels that
+ *     have no schedule, see comet_gemm_kernel, have no such limit). */
 COMET_API comet_status_t comet_w4ax_gemm_noalloc(const uint8_t* A_packed,
                                                  const uint8_t* group_prec_map,
                                                  const uint16_t* a_scales,

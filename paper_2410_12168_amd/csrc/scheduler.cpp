@@ -211,8 +211,8 @@ bool build_plan(int M, int N, int K, int G, const uint8_t* prec, const PlanOptio
 // 8192 x 8192 at 256 rows, eight slots, 62.8 us (45.5 with 128 rows), 4096 x
 // 4096, sixteen, 70.0 (34.8).  Fitted to ten layers at 160 to 2000 rows, each
 // with both heights: standard deviation 6 to 8% (128-row tiles have become 3 to 5%
-// faster since).  Below eight K-blocks nothing
-// was measured and a fixup counts the same for both.
+// faster since).  Below eight K-blocks nothing was measured and a fixup counts the
+// same for both.
 static double tile_us(int tm, int M, int N, int K, int G, int cus) {
   constexpr int kTileCols = 256;
   const PlanOptions defaults;
